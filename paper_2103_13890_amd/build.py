@@ -21,7 +21,8 @@ FLAGS = ['-O3', f'--offload-arch={ARCH}', '-std=c++17', '-fPIC', '-Wall',
          '-Wno-unused-function', '-Wno-unused-variable',
          '-Xclang', '-target-feature', '-Xclang', '-packed-fp32-ops']
 
-SOURCES = ['jfnk.hip', 'ops_f64.hip', 'ops_f32.hip', 'vec.hip', 'coarse.hip']
+SOURCES = ['jfnk.hip', 'ops_f64.hip', 'ops_f32.hip', 'vec.hip', 'coarse_f64_3d.hip', 'coarse_f64_2d.hip',
+           'coarse_f32_3d.hip', 'coarse_f32_2d.hip']
 
 
 def _hipcc():

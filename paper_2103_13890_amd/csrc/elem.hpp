@@ -79,16 +79,16 @@ template <typename T> __device__ __forceinline__ T hw_div(T a, T b) { return a /
 template <> __device__ __forceinline__ float hw_div<float>(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
 // (delta^2 + s)^e for the exponents the p-Laplacian needs
-// PF = 3: the exponent p = 3 is known at compile time; PF = 0: read p.
+// PF = 3, 1: the exponent p is known at compile time; PF = 0: read p.
 template <typename T, int PF = 0>
 __device__ __forceinline__ T plap_pow(T base, double p, int which) {
     // which 0: (p-2)/2, 1: p/2, 2: (p-4)/2
-    if (PF == 3 || p == 3.0) {
+    if (PF == 3 || (PF == 0 && p == 3.0)) {
         T r = hw_sqrt(base);
         return which == 0 ? r : (which == 1 ? base * r : hw_div(T(1), r));
     }
-    if (p == 2.0) return which == 0 ? T(1) : (which == 1 ? base : hw_div(T(1), base));
-    if (p == 1.0) {     // the minimal-surface energy: exponents -1/2, 1/2, -3/2
+    if (PF == 0 && p == 2.0) return which == 0 ? T(1) : (which == 1 ? base : hw_div(T(1), base));
+    if (PF == 1 || p == 1.0) {     // the minimal-surface energy: exponents -1/2, 1/2, -3/2
         T r = hw_sqrt(base);
         return which == 1 ? r : hw_div(T(1), which == 0 ? r : base * r);
     }
@@ -204,14 +204,14 @@ __device__ __forceinline__ void elem_plap_gauss_fd(const T *x, const T *v, T eps
         const T bx = d2 + gq_dot<DIM, T>(Gx, Gx, q) * ih2;
         const T dsq = (T(2) * gq_dot<DIM, T>(Gx, Gv, q) + eps * gq_dot<DIM, T>(Gv, Gv, q)) * ih2;
         const T bw = bx + eps * dsq;
-        if (PF == 3 || ph.a0 == 3.0) {
+        if (PF == 3 || (PF == 0 && ph.a0 == 3.0)) {
             const T kx = hw_sqrt(bx);
             kw[q] = hw_sqrt(bw);
             dk[q] = hw_div(dsq, kw[q] + kx);
-        } else if (ph.a0 == 2.0) {
+        } else if (PF == 0 && ph.a0 == 2.0) {
             kw[q] = T(1);
             dk[q] = T(0);
-        } else if (ph.a0 == 1.0) {   // k = b^(-1/2): (k_w - k_x)/eps = -dsq / (s_x s_w (s_x + s_w))
+        } else if (PF == 1 || ph.a0 == 1.0) {   // k = b^(-1/2): (k_w - k_x)/eps = -dsq / (s_x s_w (s_x + s_w))
             const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
             kw[q] = hw_div(T(1), sw);
             dk[q] = -hw_div(dsq, sx * sw * (sx + sw));
@@ -422,14 +422,14 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
         const T bx = T(ph.a1) * T(ph.a1) + qxx * ih2;
         const T dsq = (T(2) * qxv + eps * qvv) * ih2;        // (s_w - s_x) / eps
         const T bw = bx + eps * dsq;
-        if (PF == 3 || ph.a0 == 3.0) {
+        if (PF == 3 || (PF == 0 && ph.a0 == 3.0)) {
             const T kx = hw_sqrt(bx);
             kw = hw_sqrt(bw);
             dk = hw_div(dsq, kw + kx);
-        } else if (ph.a0 == 2.0) {
+        } else if (PF == 0 && ph.a0 == 2.0) {
             kw = T(1);
             dk = T(0);
-        } else if (ph.a0 == 1.0) {   // the minimal surface, k = b^(-1/2):
+        } else if (PF == 1 || ph.a0 == 1.0) {   // the minimal surface, k = b^(-1/2):
             // (k_w - k_x) / eps = -dsq / (s_x s_w (s_x + s_w)), s = sqrt(b)
             const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
             kw = hw_div(T(1), sw);

@@ -230,7 +230,8 @@ void plan(jfnk_ctx *c, Carve &cv) {
         const size_t vb0 = (size_t)g0.nn * nc * es;
         c->qn_cap = c->opt.coarse_maxit > 0 ? c->opt.coarse_maxit : (int)level_dofs(g0, nc);
         c->qn_rec = cv.take(2 * (size_t)c->qn_cap * vb0);
-        c->qn_pairs = cv.take(2 * (size_t)c->opt.coarse_qn * vb0);
+        // pair columns padded to whole wavefronts
+        c->qn_pairs = cv.take(2 * (size_t)c->opt.coarse_qn * (((size_t)g0.nn * nc + 63) / 64 * 64) * es);
         c->qn_state = (double *)cv.take(QN_STATE_LEN * sizeof(double));
     }
     const Grid gf = level_grid(c->prob, c->prob.nlevels - 1);

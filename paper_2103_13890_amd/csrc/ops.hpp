@@ -191,10 +191,12 @@ void tr_prolong_add(const Exec &, const Grid &fine, const Grid &coarse, int nc, 
 // ---- coarse solve (Algorithm 1, level 0) ------------------------------------------
 constexpr int QN_MAX = 32;   // secant pairs of the coarse L-BFGS preconditioner
 // qn_state layout: [0] 0 none / 1 built, [1] pairs kept, [2] gamma,
-// [3 + i] 1/(s_i.y_i), then s_a.y_b and y_a.y_b ([a][b], QN_MAX columns)
+// [3 + i] 1/(s_i.y_i), then s_a.y_b and y_a.y_b ([a][b], QN_MAX columns), then
+// the coefficient matrix of the small kernel ([2 QN_MAX][2 QN_MAX])
 constexpr int QN_OFF_SY = 3 + QN_MAX;
 constexpr int QN_OFF_YY = QN_OFF_SY + QN_MAX * QN_MAX;
-constexpr int QN_STATE_LEN = QN_OFF_YY + QN_MAX * QN_MAX;
+constexpr int QN_OFF_M = QN_OFF_YY + QN_MAX * QN_MAX;
+constexpr int QN_STATE_LEN = QN_OFF_M + 4 * QN_MAX * QN_MAX;
 struct CoarseArgs {
     int maxit, shift_max;
     double atol, rtol, gamma;
@@ -208,15 +210,22 @@ struct CoarseArgs {
     void *qn_rec = nullptr, *qn_pairs = nullptr;
     double *qn_state = nullptr;
 };
-// whether the coarse solve of this level runs in the one-workgroup kernel
-// that keeps the level in LDS (the one that supports the L-BFGS preconditioner)
-bool coarse_small(const Grid &, int kind, size_t elem_bytes);
-// elements of the work array the generic coarse solver needs
-size_t coarse_work_elems(const Grid &, int nc);
+// elements of the generic solver's work array: r, p, q, z and 2^d
+// contributions per element and component
+inline size_t coarse_work_elems(const Grid &g, int nc) {
+    const long long ne = (long long)g.nx * g.ny * (g.dim == 3 ? g.nz : 1);
+    return (size_t)(4 * g.nn * nc + (g.dim == 3 ? 8 : 4) * ne * nc);
+}
+template <typename T, int DIM>
+void coarse_solve_dim(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                      const double *num, const T *b, T *s, T *work, const CoarseArgs &);
 template <typename T>
-void coarse_solve(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                  const double *num, const T *b, T *s, T *work, const CoarseArgs &);
-int coarse_max_nodes();
+void coarse_solve(const Exec &ex, int mode, const Grid &g, const Phys &ph, const T *kap, const T *x, const T *Ax,
+                  const double *num, const T *b, T *s, T *work, const CoarseArgs &ca) {
+    if (g.dim == 2) coarse_solve_dim<T, 2>(ex, mode, g, ph, kap, x, Ax, num, b, s, work, ca);
+    else coarse_solve_dim<T, 3>(ex, mode, g, ph, kap, x, Ax, num, b, s, work, ca);
+}
+inline int coarse_max_nodes() { return 1 << 16; }
 
 // ---- loads ---------------------------------------------------------------------------
 void load_gaussians(const Exec &, const Grid &, const double *prm, int count, double *b);

@@ -48,6 +48,24 @@ __device__ __forceinline__ double wave_sum(double v) {
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
+// Sum over the lane's row of 16 lanes, the same value in every lane of the row.
+__device__ __forceinline__ double row_sum(double v) {
+    v += dpp_mov<0xB1>(v);
+    v += dpp_mov<0x4E>(v);
+    v += dpp_mov<0x141>(v);
+    v += dpp_mov<0x140>(v);
+    return v;
+}
+
+// Sum of the wave totals in scratch[0..nw), nw <= MAX_WAVES = 16, after the
+// barrier that follows their writes: lane l of every row of 16 reads total l
+// and the row adds them by DPP, so a total costs one LDS read instead of a
+// loop of nw dependent ones.
+__device__ __forceinline__ double waves_total(const double *scratch, int nw) {
+    const int l = threadIdx.x & 15;
+    return row_sum(l < nw ? scratch[l] : 0.0);
+}
+
 // Sum NS values over the block; the totals land in tot[0..NS) (shared).
 // blockDim.x must be a multiple of 64.
 template <int NS>
@@ -68,8 +86,7 @@ __device__ __forceinline__ void block_sum(double (&v)[NS], double *scratch, doub
     __syncthreads();
 }
 
-// One value summed over the block with a single barrier: every thread reads
-// the wave totals (an LDS broadcast) and adds them in wave order.  scratch
+// One value summed over the block with a single barrier.  scratch
 // (MAX_WAVES entries) must not be written again until every thread of the
 // block has passed a later barrier: callers that sum repeatedly alternate
 // two scratch arrays.
@@ -78,9 +95,7 @@ __device__ __forceinline__ double block_sum1(double v, double *scratch) {
     v = wave_sum(v);
     if (lane == 0) scratch[wid] = v;
     __syncthreads();
-    double s = 0.0;
-    for (int w = 0; w < nw; ++w) s += scratch[w];
-    return s;
+    return waves_total(scratch, nw);
 }
 
 // Per-block partial sums: the block's totals go to part[blockIdx.x * NS + k].
