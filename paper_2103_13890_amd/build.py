@@ -21,8 +21,12 @@ FLAGS = ['-O3', f'--offload-arch={ARCH}', '-std=c++17', '-fPIC', '-Wall',
          '-Wno-unused-function', '-Wno-unused-variable',
          '-Xclang', '-target-feature', '-Xclang', '-packed-fp32-ops']
 
-SOURCES = ['jfnk.hip', 'ops_f64.hip', 'ops_f32.hip', 'vec.hip', 'coarse_f64_3d.hip', 'coarse_f64_2d.hip',
-           'coarse_f32_3d.hip', 'coarse_f32_2d.hip']
+# the longest compilations first
+SOURCES = ['stencil_f64_gauss.hip', 'stencil_f64_plap.hip', 'stencil_f64_bratu.hip',
+           'stencil_f64_neohooke.hip', 'stencil_f64_invcoef.hip', 'coarse_f64_3d.hip', 'coarse_f64_2d.hip',
+           'stencil_f32_gauss.hip', 'stencil_f32_plap.hip', 'stencil_f32_bratu.hip',
+           'stencil_f32_neohooke.hip', 'stencil_f32_invcoef.hip', 'coarse_f32_3d.hip', 'coarse_f32_2d.hip',
+           'ops_f64.hip', 'jfnk.hip', 'vec.hip']
 
 
 def _hipcc():

@@ -60,8 +60,9 @@ __device__ __forceinline__ void node_coords(const Grid &g, long long i, int &x, 
 }
 
 // Evaluation modes of the stencil kernels: the residual A(x), the FD
-// quotient from two residual evaluations, or its element difference form.
-enum { M_RESID = 0, M_FD_PLAIN = 1, M_FD_DIFF = 2 };
+// quotient from two residual evaluations, its element difference form, or
+// the exact transposed Jacobian J(x)^T v.
+enum { M_RESID = 0, M_FD_PLAIN = 1, M_FD_DIFF = 2, M_VJP = 3 };
 
 template <typename T> struct Prec;
 template <> struct Prec<double> {

@@ -90,6 +90,9 @@ struct jfnk_ctx {
     int qn_cap = 0;
     // pinned host copies of the power method's slot pairs, one event each
     double *hpin = nullptr;
+    // scratch of the Neo-Hookean element kernel, sized for FP64 on the finest level
+    void *nh = nullptr;
+    size_t nh_bytes = 0;
     hipEvent_t pev[3] = {nullptr, nullptr, nullptr};
 };
 
@@ -252,6 +255,12 @@ void plan(jfnk_ctx *c, Carve &cv) {
     c->tmpB = (double *)cv.take(fb);
     c->kap64 = c->prob.kind == JFNK_INVCOEF ? (double *)cv.take((size_t)gf.nn * sizeof(double)) : nullptr;
     c->mf = c->prob.kind == JFNK_INVCOEF ? (double *)cv.take((size_t)gf.nn * sizeof(double)) : nullptr;
+    if (nc == 3) {
+        // (a coarser level may take the split kernel's larger entries)
+        for (int l = 0; l < c->prob.nlevels; ++l)
+            c->nh_bytes = std::max(c->nh_bytes, nh_scratch_entries(c->lev[l].g) * sizeof(double));
+        c->nh = cv.take(c->nh_bytes);
+    }
     // basis columns start on 512-byte boundaries (the Gram-Schmidt and
     // combine kernels then read two adjacent entries per 16-byte access)
     c->ldv = (c->n + 63) / 64 * 64;
@@ -372,7 +381,7 @@ template <typename T> jfnk_status power_method(jfnk_ctx *c, int l) {
     auto queue = [&](int k) -> jfnk_status {
         const double *n2 = k == 1 ? lslot(c, l, L_V) : lslot(c, l, pq[(k - 1) % 3] + 1);
         double *out = lslot(c, l, pq[k % 3]);
-        op_power<T>(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), buf[(k - 1) % 4],
+        ops<T>(c->ph).power(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), buf[(k - 1) % 4],
                     lslot(c, l, L_NUM), n2, buf[k % 4], out);
         CHK(check_launch(c));
         HIPCHK(c, hipMemcpyAsync(c->hpin + 2 * (k % 3), out, 2 * sizeof(double), hipMemcpyDeviceToHost, c->st));
@@ -458,7 +467,7 @@ template <typename T> jfnk_status setup_levels(jfnk_ctx *c, const double *u, con
     for (int l = 0; l <= Lf; ++l) {
         Level &L = c->lev[l];
         // T* scratch for F: use t
-        op_residual<T>(c->ex, L.g, c->ph, CP<T>(L.kap), CP<T>(L.x), nullptr, P<T>(L.t), P<T>(L.Ax), nullptr);
+        ops<T>(c->ph).residual(c->ex, L.g, c->ph, CP<T>(L.kap), CP<T>(L.x), nullptr, P<T>(L.t), P<T>(L.Ax), nullptr);
         c->ge[l] += 1;
         vec_eps_num<T>(c->ex, L.g, nc, CP<T>(L.x), root_eps(c, c->vprec, mg_mode(c)), c->opt.eps_mode,
                        lslot(c, l, L_NUM));
@@ -524,7 +533,7 @@ void chebyshev(jfnk_ctx *c, int l, const T *b, T *s, int nu, bool zero, T *out, 
             b_n2 = lslot(c, l, L_B);
         }
         const double rn = 1.0 / (2.0 * k.sigma - rho);
-        op_cheb_first<T>(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), b, lslot(c, l, L_NUM),
+        ops<T>(c->ph).cheb_first(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), b, lslot(c, l, L_NUM),
                          b_n2, P<T>(L.r), s, P<T>(L.d[1]), 1.0 / k.theta, rn * rho, 2.0 * rn / k.delta,
                          lslot(c, l, L_D1));
         c->ge[l] += 1;
@@ -533,7 +542,7 @@ void chebyshev(jfnk_ctx *c, int l, const T *b, T *s, int nu, bool zero, T *out, 
     } else if (zero) {
         vec_cheb_zero<T>(c->ex, g, nc, b, P<T>(L.r), P<T>(L.d[0]), s, 1.0 / k.theta, lslot(c, l, L_D0));
     } else {
-        op_cheb_init<T>(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), s, lslot(c, l, L_NUM),
+        ops<T>(c->ph).cheb_init(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), s, lslot(c, l, L_NUM),
                         lslot(c, l, L_S), b, P<T>(L.r), P<T>(L.d[0]), 1.0 / k.theta, lslot(c, l, L_D0));
         c->ge[l] += 1;
     }
@@ -542,7 +551,7 @@ void chebyshev(jfnk_ctx *c, int l, const T *b, T *s, int nu, bool zero, T *out, 
         const double rn = 1.0 / (2.0 * k.sigma - rho);
         const double c1 = rn * rho, c2 = 2.0 * rn / k.delta;
         if (it == nu - 2) {
-            op_cheb_last<T>(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), CP<T>(L.d[cur]),
+            ops<T>(c->ph).cheb_last(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), CP<T>(L.d[cur]),
                             lslot(c, l, L_NUM), lslot(c, l, cur ? L_D1 : L_D0), CP<T>(L.r), s, out, c1, c2, out_n2);
             c->ge[l] += 1;
             return;
@@ -550,7 +559,7 @@ void chebyshev(jfnk_ctx *c, int l, const T *b, T *s, int nu, bool zero, T *out, 
         {
             // the timer brackets the interior steps only (28 B/node each)
             TimeScope ts(c, fine ? JFNK_TIMER_CHEB_FINE : JFNK_TIMER_COUNT);
-            op_cheb_step<T>(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), CP<T>(L.d[cur]),
+            ops<T>(c->ph).cheb_step(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), CP<T>(L.d[cur]),
                             lslot(c, l, L_NUM), lslot(c, l, cur ? L_D1 : L_D0), P<T>(L.r), s, P<T>(L.d[1 - cur]),
                             c1, c2, lslot(c, l, cur ? L_D0 : L_D1));
         }
@@ -590,7 +599,7 @@ void vcycle(jfnk_ctx *c, int l, const T *b, T *s_out, double *s_out_n2, const do
     // pre-smoothing from s = 0; s and ||s||^2 (L_S) materialised
     chebyshev<T>(c, l, b, s, c->opt.nu_pre, true, s, lslot(c, l, L_S), b_n2);
     // r_{l-1} = R (b - J s)
-    op_resid_jv<T>(c->ex, mg_mode(c), L.g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), s, lslot(c, l, L_NUM),
+    ops<T>(c->ph).resid_jv(c->ex, mg_mode(c), L.g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), s, lslot(c, l, L_NUM),
                    lslot(c, l, L_S), b, P<T>(L.t));
     c->ge[l] += 1;
     Level &C = c->lev[l - 1];
@@ -845,7 +854,7 @@ jfnk_status eval_residual(jfnk_ctx *c, const double *s, double *Fo, double *Ao, 
     const Level &L = c->lev[c->L];
     {
         TimeScope ts(c, timed ? JFNK_TIMER_RESID_FINE : JFNK_TIMER_COUNT);
-        op_residual<double>(c->ex, L.g, c->ph, c->kap64, s, c->bm, Fo, Ao, slot(c, sl));
+        ops<double>(c->ph).residual(c->ex, L.g, c->ph, c->kap64, s, c->bm, Fo, Ao, slot(c, sl));
     }
     c->ge[c->L] += 1;
     return check_launch(c);
@@ -1129,6 +1138,8 @@ jfnk_status jfnk_create(const jfnk_problem *p, const jfnk_options *o, void *ws, 
     c->ex.st = c->st;
     c->ex.red.part = c->part;
     c->ex.path = o->kernel_path;
+    c->ex.nh = c->nh;
+    c->ex.nh_bytes = c->nh_bytes;
     // deferred reductions: the norms that only the next FD evaluation reads
     // (Chebyshev directions, smoothed corrections, restricted loads, the
     // preconditioned direction of the outer Krylov step)
@@ -1192,10 +1203,10 @@ jfnk_status jfnk_residual(jfnk_ctx *c, int level, int prec, const void *u, const
     if (prec == JFNK_F64) {
         const double *k = coef_kap<double>(c, level, (const double *)coef, c->tmpB);
         TimeScope ts(c, level == c->L ? JFNK_TIMER_RESID_FINE : JFNK_TIMER_COUNT);
-        op_residual<double>(c->ex, g, c->ph, k, (const double *)u, (const double *)b, (double *)F, nullptr, nullptr);
+        ops<double>(c->ph).residual(c->ex, g, c->ph, k, (const double *)u, (const double *)b, (double *)F, nullptr, nullptr);
     } else {
         const float *k = coef_kap<float>(c, level, (const double *)coef, (float *)c->tmpB);
-        op_residual<float>(c->ex, g, c->ph, k, (const float *)u, (const float *)b, (float *)F, nullptr, nullptr);
+        ops<float>(c->ph).residual(c->ex, g, c->ph, k, (const float *)u, (const float *)b, (float *)F, nullptr, nullptr);
     }
     return check_launch(c);
 }
@@ -1217,7 +1228,7 @@ jfnk_status jfnk_residual_static(const jfnk_problem *p, int level, const double 
     ex.red = Red{part};
     ex.path = 0;
     ex.red_cap = STATIC_SCRATCH_DOUBLES;
-    op_residual<double>(ex, level_grid(*p, level), make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
+    ops<double>(make_phys(*p)).residual(ex, level_grid(*p, level), make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
     if (ex.red_short)
         return fail(nullptr, JFNK_E_INVAL, "the grid needs more partial sums than the static scratch holds ("
                     + std::to_string(STATIC_SCRATCH_DOUBLES) + "): use jfnk_residual");
@@ -1257,7 +1268,7 @@ jfnk_status jfnk_jv(jfnk_ctx *c, int level, int prec, const void *u, const void 
         const double *k = coef_kap<double>(c, level, (const double *)coef, c->tmpB);
         const double *A = (const double *)Au;
         if (!A) {
-            op_residual<double>(c->ex, g, c->ph, k, (const double *)u, nullptr, c->tmpA, nullptr, nullptr);
+            ops<double>(c->ph).residual(c->ex, g, c->ph, k, (const double *)u, nullptr, c->tmpA, nullptr, nullptr);
             A = c->tmpA;
         }
         vec_eps_num<double>(c->ex, g, nc, (const double *)u, root_eps(c, JFNK_F64, outer_mode(c)), c->opt.eps_mode,
@@ -1269,7 +1280,7 @@ jfnk_status jfnk_jv(jfnk_ctx *c, int level, int prec, const void *u, const void 
         const float *k = coef_kap<float>(c, level, (const double *)coef, (float *)c->tmpB);
         const float *A = (const float *)Au;
         if (!A) {
-            op_residual<float>(c->ex, g, c->ph, k, (const float *)u, nullptr, (float *)c->tmpA, nullptr, nullptr);
+            ops<float>(c->ph).residual(c->ex, g, c->ph, k, (const float *)u, nullptr, (float *)c->tmpA, nullptr, nullptr);
             A = (const float *)c->tmpA;
         }
         vec_eps_num<float>(c->ex, g, nc, (const float *)u, root_eps(c, JFNK_F32, outer_mode(c)), c->opt.eps_mode,

@@ -1,6 +1,8 @@
 // Host-side launch interface of libjfnk's kernels.  Every function queues
 // work on ex.st and returns immediately; slots are device doubles.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 #include "reduce.hpp"
 
@@ -16,6 +18,10 @@ struct Exec {
     // (the context's workspace sizes red for every launch it makes)
     long long red_cap = 0;
     mutable bool red_short = false;
+    // scratch of the Neo-Hookean element kernel (nullable: without it the
+    // levels run node-centric)
+    void *nh = nullptr;
+    size_t nh_bytes = 0;
     bool red_fits(int nb, int ns) const {
         if (red_cap <= 0 || (long long)nb * (ns > 0 ? ns : 1) <= red_cap) return true;
         red_short = true;
@@ -76,46 +82,72 @@ inline FdStep make_fd(const Exec &ex, const double *num, const double *vn2, doub
     return f;
 }
 
-// a1 residual: F = A(u) - b (b nullable), A(u) -> Aout (nullable), ||F||^2 -> nrm2 (nullable)
-template <typename T>
-void op_residual(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *b, T *F, T *Aout,
-                 double *nrm2);
+inline int node_blocks(long long n) {
+    long long b = (n + BLOCK - 1) / BLOCK;
+    if (b > 4096) b = 4096;
+    return (int)(b < 1 ? 1 : b);
+}
+
+// entries of the scratch that the Neo-Hookean element kernel writes on a level
+size_t nh_scratch_entries(const Grid &);
+
+// The stencil launchers of one precision and kind (a source file each).
+// residual, a1: F = A(u) - b (b nullable), A(u) -> Aout (nullable), ||F||^2 ->
+//   nrm2 (nullable)
 // FD evaluations (Sec. 1) take mode = M_FD_PLAIN ((A(x + eps v) - Ax)/eps
-// with the cached Ax) or M_FD_DIFF (the element difference form; Ax unused).
-// a5 FD Jacobian action
+// with the cached Ax) or M_FD_DIFF (the element difference form; Ax unused):
+// jv, a5: FD Jacobian action; jv_mixed: FP64 state, FP32 direction
+// cheb_step, a6: Chebyshev step with d_k (||d_k||^2 in vn2): s += d; r -= J d;
+//   dn = c1 d + c2 r
+// cheb_first: first step from s = 0 with the direction b (||b||^2 in vn2):
+//   s = b / theta, r = b - (J b) / theta, dn = c1 s + c2 r; ||dn||^2 -> dn_nrm2
+// cheb_last: last step with d_k: sout = s + d_k + (c1 d_k + c2 (r - J d_k));
+//   ||sout||^2 -> s_nrm2 (nullable).  sout may alias s.
+// cheb_init: start from s: r = b - J s, d = r / theta
+// resid_jv, a7: residual of the correction, t = b - J s
+// power, a4: power step: q = J v, out[0] = v.q, out[1] = ||q||^2
+template <typename T> struct StencilTable {
+    void (*residual)(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *b, T *F, T *Aout,
+                     double *nrm2);
+    void (*jv)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax, const T *v,
+               const double *num, const double *vn2, double eps_fixed, T *Jv);
+    void (*cheb_step)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                      const T *d, const double *num, const double *vn2, T *r, T *s, T *dn, double c1, double c2,
+                      double *dn_nrm2);
+    void (*cheb_first)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                       const T *b, const double *num, const double *vn2, T *r, T *s, T *dn, double inv_theta,
+                       double c1, double c2, double *dn_nrm2);
+    void (*cheb_last)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                      const T *d, const double *num, const double *vn2, const T *r, const T *s, T *sout, double c1,
+                      double c2, double *s_nrm2);
+    void (*cheb_init)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                      const T *s, const double *num, const double *vn2, const T *b, T *r, T *d, double inv_theta,
+                      double *d_nrm2);
+    void (*resid_jv)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                     const T *s, const double *num, const double *vn2, const T *b, T *t);
+    void (*power)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                  const T *v, const double *num, const double *vn2, T *q, double *out);
+    void (*jv_mixed)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
+                     const float *v, const double *num, const double *vn2, double eps_fixed, T *Jv);
+    // a13 (FP64): exact J(u)^T lam on the DoFs
+    void (*vjp)(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *lam, T *out);
+};
+template <typename T, int KIND> const StencilTable<T> *stencil_table();
+template <typename T> inline const StencilTable<T> &ops(const Phys &ph) {
+    switch (ph.kind) {
+    case JFNK_BRATU: return *stencil_table<T, JFNK_BRATU>();
+    case JFNK_PLAP: return *stencil_table<T, JFNK_PLAP>();
+    case JFNK_INVCOEF: return *stencil_table<T, JFNK_INVCOEF>();
+    case JFNK_NEOHOOKE: return *stencil_table<T, JFNK_NEOHOOKE>();
+    default: return *stencil_table<T, JFNK_PLAP_GAUSS>();
+    }
+}
 template <typename T, typename TV>
-void op_jv(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax, const TV *v,
-           const double *num, const double *vn2, double eps_fixed, T *Jv);
-// a6 Chebyshev step with d_k (||d_k||^2 in vn2): s += d; r -= J d; dn = c1 d + c2 r
-template <typename T>
-void op_cheb_step(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                  const T *d, const double *num, const double *vn2, T *r, T *s, T *dn, double c1, double c2,
-                  double *dn_nrm2);
-// first Chebyshev step from s = 0 with the direction b (||b||^2 in vn2):
-// s = b / theta, r = b - (J b) / theta, dn = c1 s + c2 r; ||dn||^2 -> dn_nrm2
-template <typename T>
-void op_cheb_first(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                   const T *b, const double *num, const double *vn2, T *r, T *s, T *dn, double inv_theta, double c1,
-                   double c2, double *dn_nrm2);
-// last Chebyshev step with d_k: sout = s + d_k + (c1 d_k + c2 (r - J d_k));
-// ||sout||^2 -> s_nrm2 (nullable).  sout may alias s.
-template <typename T>
-void op_cheb_last(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                  const T *d, const double *num, const double *vn2, const T *r, const T *s, T *sout, double c1,
-                  double c2, double *s_nrm2);
-// Chebyshev start from s: r = b - J s, d = r / theta
-template <typename T>
-void op_cheb_init(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                  const T *s, const double *num, const double *vn2, const T *b, T *r, T *d, double inv_theta,
-                  double *d_nrm2);
-// a7 residual of the correction: t = b - J s
-template <typename T>
-void op_resid_jv(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                 const T *s, const double *num, const double *vn2, const T *b, T *t);
-// a4 power step: q = J v, out[0] = v.q, out[1] = ||q||^2
-template <typename T>
-void op_power(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax, const T *v,
-              const double *num, const double *vn2, T *q, double *out);
+inline void op_jv(const Exec &ex, int mode, const Grid &g, const Phys &ph, const T *kap, const T *x, const T *Ax,
+                  const TV *v, const double *num, const double *vn2, double eps_fixed, T *Jv) {
+    if constexpr (std::is_same<T, TV>::value) ops<T>(ph).jv(ex, mode, g, ph, kap, x, Ax, v, num, vn2, eps_fixed, Jv);
+    else ops<T>(ph).jv_mixed(ex, mode, g, ph, kap, x, Ax, v, num, vn2, eps_fixed, Jv);
+}
 
 // energy Psi_h(u) (element sum) -> out[0]   (FP64, variational kinds)
 void op_energy(const Exec &, const Grid &, const Phys &, const double *u, double *out);

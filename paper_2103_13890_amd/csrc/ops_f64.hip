@@ -1,17 +1,11 @@
-// FP64 instantiation of the stencil launchers, the mixed-precision outer
-// Jacobian action (FP64 state, FP32 preconditioned direction), the energy
+// FP64 element sums and products outside the stencil launchers: the energy
 // and the exact vector-Jacobian products.
-#define JFNK_T double
-#include "ops_stencil.inc"
+#include "stencil_nh.hpp"
+#include "ops.hpp"
 
 namespace jfnk {
 
-template <>
-void op_jv<double, float>(const Exec &ex, int mode, const Grid &g, const Phys &ph, const double *kap,
-                          const double *x, const double *Ax, const float *v, const double *num, const double *vn2,
-                          double eps_fixed, double *Jv) {
-    dispatch_fd<double, float, EpiJv>(ex, mode, g, ph, kap, x, v, Ax, make_fd(ex, num, vn2, eps_fixed), Jv, g.nn);
-}
+size_t nh_scratch_entries(const Grid &g) { return nh_entries(g); }
 
 // ---- energy: sum over elements of Psi_e(u) ----------------------------------
 template <int DIM, int KIND>
@@ -62,7 +56,7 @@ template <int DIM, int KIND>
 __global__ __launch_bounds__(BLOCK) void k_vjp(Grid g, Phys ph, const double *kap, const double *u,
                                                const double *lam, int wrt, double scale, double *out) {
     constexpr int NV = Cell<DIM>::NV;
-    constexpr int NC = (KIND == JFNK_NEOHOOKE) ? 3 : 1;
+    constexpr int NC = 1;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < g.nn; i += stride) {
         int x, y, z;
@@ -93,12 +87,7 @@ __global__ __launch_bounds__(BLOCK) void k_vjp(Grid g, Phys ph, const double *ka
                 }
                 kp[a] = (KIND == JFNK_INVCOEF) ? kap[j] : 0.0;
             }
-            if constexpr (KIND == JFNK_NEOHOOKE) {
-                double r[3][8];
-                elem_neohooke_jvp<double>(w, l, ph, g.h, r);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[c] += r[c][e];
-            } else if (KIND == JFNK_INVCOEF) {
+            if (KIND == JFNK_INVCOEF) {
                 if (wrt == 1) {
                     acc[0] += elem_coef_factor<DIM, double>(w[0], l[0], g.h);
                 } else {
@@ -134,9 +123,7 @@ void op_vjp(const Exec &ex, const Grid &g, const Phys &ph, const double *kap, co
         if (g.dim == 2) k_vjp<2, JFNK_INVCOEF><<<nb, BLOCK, 0, ex.st>>>(g, ph, kap, u, lam, wrt, scale, out);
         else k_vjp<3, JFNK_INVCOEF><<<nb, BLOCK, 0, ex.st>>>(g, ph, kap, u, lam, wrt, scale, out);
         break;
-    case JFNK_NEOHOOKE:
-        k_vjp<3, JFNK_NEOHOOKE><<<nb, BLOCK, 0, ex.st>>>(g, ph, kap, u, lam, wrt, scale, out);
-        break;
+    case JFNK_NEOHOOKE: ops<double>(ph).vjp(ex, g, ph, kap, u, lam, out); break;
     case JFNK_PLAP_GAUSS:
         if (g.dim == 2) k_vjp<2, JFNK_PLAP_GAUSS><<<nb, BLOCK, 0, ex.st>>>(g, ph, kap, u, lam, wrt, scale, out);
         else k_vjp<3, JFNK_PLAP_GAUSS><<<nb, BLOCK, 0, ex.st>>>(g, ph, kap, u, lam, wrt, scale, out);

@@ -307,30 +307,15 @@ template <class E> __device__ __forceinline__ double fd_eps_prepare(const FdStep
 template <int DIM, int KIND, int MODE, typename T, int NC, int NV, int PF = 0>
 __device__ __forceinline__ void elem_eval(const T (*xe)[NV], const T (*ve)[NV], const T *kp, T eps,
                                           const Phys &ph, T h, T (*r)[NV], T m = T(1)) {
-    if constexpr (KIND == JFNK_NEOHOOKE) {
-        if constexpr (MODE == M_FD_DIFF) {
-            elem_neohooke_fd<T>(xe, ve, eps, ph, h, r);
-        } else if constexpr (MODE == M_FD_PLAIN) {
-            T w[3][8];
+    if constexpr (MODE == M_FD_DIFF) {
+        elem_scalar_fd<DIM, KIND, T, PF>(xe[0], ve[0], kp, eps, ph, h, r[0], m);
+    } else if constexpr (MODE == M_FD_PLAIN) {
+        T w[NV];
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int a = 0; a < 8; ++a) w[c][a] = xe[c][a] + eps * ve[c][a];
-            elem_neohooke<T>(w, ph, h, r);
-        } else {
-            elem_neohooke<T>(xe, ph, h, r);
-        }
+        for (int a = 0; a < NV; ++a) w[a] = xe[0][a] + eps * ve[0][a];
+        elem_scalar<DIM, KIND, T, PF>(w, kp, ph, h, r[0], m);
     } else {
-        if constexpr (MODE == M_FD_DIFF) {
-            elem_scalar_fd<DIM, KIND, T, PF>(xe[0], ve[0], kp, eps, ph, h, r[0], m);
-        } else if constexpr (MODE == M_FD_PLAIN) {
-            T w[NV];
-#pragma unroll
-            for (int a = 0; a < NV; ++a) w[a] = xe[0][a] + eps * ve[0][a];
-            elem_scalar<DIM, KIND, T, PF>(w, kp, ph, h, r[0], m);
-        } else {
-            elem_scalar<DIM, KIND, T, PF>(xe[0], kp, ph, h, r[0], m);
-        }
+        elem_scalar<DIM, KIND, T, PF>(xe[0], kp, ph, h, r[0], m);
     }
 }
 
@@ -398,53 +383,10 @@ __device__ __forceinline__ void node_value_scalar(const Grid &g, const Phys &ph,
     if constexpr (MODE == M_FD_PLAIN) val[0] = (val[0] - Ax[i]) * (T)(1.0 / eps);
 }
 
-template <int DIM, int KIND, int MODE, typename T, typename TV>
-__device__ __forceinline__ void node_value(const Grid &g, const Phys &ph, const T *kap, const T *x, const TV *v,
-                                           const T *Ax, double eps, int X, int Y, int Z, long long i, T *val) {
-    constexpr int NV = Cell<DIM>::NV;
-    constexpr int NC = (KIND == JFNK_NEOHOOKE) ? 3 : 1;
-    if constexpr (NC == 1) {
-        node_value_scalar<DIM, KIND, MODE, T, TV>(g, ph, kap, x, v, Ax, eps, X, Y, Z, i, val);
-        return;
-    }
-    const long long nn = g.nn;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) val[c] = T(0);
-    if (MODE != M_RESID && eps == 0.0) return;
-    const T h = (T)g.h;
-    const T e = (T)eps;
-    for (int el = 0; el < NV; ++el) {
-        const int ex = X - (el & 1), ey = Y - ((el >> 1) & 1), ez = (DIM == 3) ? Z - ((el >> 2) & 1) : 0;
-        if (ex < 0 || ex >= g.nx || ey < 0 || ey >= g.ny) continue;
-        if (DIM == 3 && (ez < 0 || ez >= g.nz)) continue;
-        T xe[NC][NV], ve[NC][NV], kp[NV], r[NC][NV];
-#pragma unroll
-        for (int a = 0; a < NV; ++a) {
-            const int ax = ex + (a & 1), ay = ey + ((a >> 1) & 1), az = ez + ((a >> 2) & 1);
-            const long long j = node_index(g, ax, ay, az);
-            const bool dj = (MODE != M_RESID) && is_dirichlet(g, ax, ay, az);
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                xe[c][a] = x[c * nn + j];
-                ve[c][a] = (MODE == M_RESID || dj) ? T(0) : (T)v[c * nn + j];
-            }
-            kp[a] = (KIND == JFNK_INVCOEF) ? kap[j] : T(0);
-        }
-        elem_eval<DIM, KIND, MODE, T, NC, NV>(xe, ve, kp, e, ph, h, r);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) val[c] += r[c][el];
-    }
-    if constexpr (MODE == M_FD_PLAIN) {
-        const T ie = (T)(1.0 / eps);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) val[c] = (val[c] - Ax[c * nn + i]) * ie;
-    }
-}
-
 template <int DIM, int KIND, int MODE, typename T, typename TV, class Epi>
 __global__ __launch_bounds__(BLOCK) void k_node(Grid g, Phys ph, const T *kap, const T *x, const TV *v, const T *Ax,
                                                 FdStep fd, Epi epi, Red red) {
-    constexpr int NC = (KIND == JFNK_NEOHOOKE) ? 3 : 1;
+    constexpr int NC = 1;
     const double eps = fd_eps_prepare(fd, epi);
     double sums[Epi::NS > 0 ? Epi::NS : 1];
 #pragma unroll
@@ -457,7 +399,7 @@ __global__ __launch_bounds__(BLOCK) void k_node(Grid g, Phys ph, const T *kap, c
         T val[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) val[c] = T(0);
-        if (!dir) node_value<DIM, KIND, MODE, T, TV>(g, ph, kap, x, v, Ax, eps, X, Y, Z, i, val);
+        if (!dir) node_value_scalar<DIM, KIND, MODE, T, TV>(g, ph, kap, x, v, Ax, eps, X, Y, Z, i, val);
         T in[Epi::NIN * NC > 0 ? Epi::NIN * NC : 1];
         const PtrAt at{i};
         epi.load(at, in);
@@ -535,89 +477,6 @@ __global__ __launch_bounds__(BLOCK) void k_node_split(Grid g, Phys ph, const T *
                 if (eval) val[0] = (val[0] - Ax[i]) * (T)(1.0 / eps);
             }
             T in[Epi::NIN > 0 ? Epi::NIN : 1];
-            const PtrAt at{i};
-            epi.load(at, in);
-            epi.node(at, val, dir, sums, in);
-        }
-    }
-    if constexpr (Epi::NS > 0) block_partials<Epi::NS>(sums, red);
-}
-
-// Node values of the Neo-Hookean kind with one wavefront per node: lane l
-// evaluates Gauss point l & 7 of element l >> 3 around the node (the
-// element whose corner l >> 3 the node is), and the wave sums the 64 parts
-// by DPP in a fixed order.  A node's 8 elements x 8 points run in parallel
-// instead of in one lane's sequence, which bounded every level of the
-// node-centric Neo-Hookean hierarchy by one thread's latency.  Every lane of
-// a wave walks the same nodes, so the sums are wave-uniform; lane 0 applies
-// the epilogue.
-template <int MODE, typename T, typename TV, class Epi>
-__global__ __launch_bounds__(BLOCK) void k_node_nh(Grid g, Phys ph, const T *x, const TV *v, const T *Ax,
-                                                   FdStep fd, Epi epi, Red red) {
-    constexpr int NC = 3;
-    const double eps = fd_eps_prepare(fd, epi);
-    double sums[Epi::NS > 0 ? Epi::NS : 1];
-#pragma unroll
-    for (int k = 0; k < (Epi::NS > 0 ? Epi::NS : 1); ++k) sums[k] = 0.0;
-    const long long nn = g.nn;
-    const int lane = threadIdx.x & 63;
-    const int el = lane >> 3, gq = lane & 7;
-    const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const long long nwaves = ((long long)gridDim.x * blockDim.x) >> 6;
-    const T h = (T)g.h, e = (T)eps;
-    for (long long i = wave; i < nn; i += nwaves) {
-        int X, Y, Z;
-        node_coords(g, i, X, Y, Z);
-        const bool dir = is_dirichlet(g, X, Y, Z);
-        const bool eval = !dir && !(MODE != M_RESID && eps == 0.0);
-        const int ex = X - (el & 1), ey = Y - ((el >> 1) & 1), ez = Z - ((el >> 2) & 1);
-        const bool inside = eval && ex >= 0 && ex < g.nx && ey >= 0 && ey < g.ny && ez >= 0 && ez < g.nz;
-        T c3[NC] = {T(0), T(0), T(0)};
-        if (inside) {
-            T xe[NC][8], ve[NC][8], r8[NC][8];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const int ax = ex + (a & 1), ay = ey + ((a >> 1) & 1), az = ez + ((a >> 2) & 1);
-                const long long j = node_index(g, ax, ay, az);
-                const bool dj = (MODE != M_RESID) && is_dirichlet(g, ax, ay, az);
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    xe[c][a] = x[c * nn + j];
-                    ve[c][a] = (MODE == M_RESID || dj) ? T(0) : (T)v[c * nn + j];
-                    r8[c][a] = T(0);
-                }
-            }
-            if constexpr (MODE == M_FD_DIFF) {
-                nh_point_fd<T>(xe, ve, e, ph, h, gq, r8);
-            } else if constexpr (MODE == M_FD_PLAIN) {
-                T w[NC][8];
-#pragma unroll
-                for (int c = 0; c < NC; ++c)
-#pragma unroll
-                    for (int a = 0; a < 8; ++a) w[c][a] = xe[c][a] + e * ve[c][a];
-                nh_point<T>(w, ph, h, gq, r8);
-            } else {
-                nh_point<T>(xe, ph, h, gq, r8);
-            }
-#pragma unroll
-            for (int a = 0; a < 8; ++a)
-                if (a == el) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) c3[c] = r8[c][a];
-                }
-        }
-        T val[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) val[c] = (T)wave_sum((double)c3[c]);
-        if (lane == 0) {
-            if constexpr (MODE == M_FD_PLAIN) {
-                if (eval) {
-                    const T ie = (T)(1.0 / eps);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) val[c] = (val[c] - Ax[c * nn + i]) * ie;
-                }
-            }
-            T in[Epi::NIN * NC > 0 ? Epi::NIN * NC : 1];
             const PtrAt at{i};
             epi.load(at, in);
             epi.node(at, val, dir, sums, in);

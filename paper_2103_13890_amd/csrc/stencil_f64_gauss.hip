@@ -1,0 +1,5 @@
+// Stencil launchers: JFNK_PLAP_GAUSS, F64 levels and the outer FP64 operator.
+#define JFNK_T double
+#define JFNK_KIND_ID JFNK_PLAP_GAUSS
+#define JFNK_JV_MIXED Ops::jv<float>
+#include "ops_stencil.inc"
