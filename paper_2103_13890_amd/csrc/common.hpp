@@ -60,9 +60,10 @@ __device__ __forceinline__ void node_coords(const Grid &g, long long i, int &x, 
 }
 
 // Evaluation modes of the stencil kernels: the residual A(x), the FD
-// quotient from two residual evaluations, its element difference form, or
-// the exact transposed Jacobian J(x)^T v.
-enum { M_RESID = 0, M_FD_PLAIN = 1, M_FD_DIFF = 2, M_VJP = 3 };
+// quotient from two residual evaluations, its element difference form, the
+// exact transposed Jacobian J(x)^T v, or the coefficient's (dA/dm)^T v without
+// its factor e^m (INVCOEF; at every node).
+enum { M_RESID = 0, M_FD_PLAIN = 1, M_FD_DIFF = 2, M_VJP = 3, M_COEF = 4 };
 
 template <typename T> struct Prec;
 template <> struct Prec<double> {

@@ -236,7 +236,7 @@ __device__ __forceinline__ void elem_plap_gauss_fd(const T *x, const T *v, T eps
 
 // PLAP_GAUSS exact J_e lam (symmetric): per Gauss point
 // k_q g_lam + (p - 2) (delta^2 + |g|^2)^((p-4)/2) (g . g_lam) g
-template <int DIM, typename T>
+template <int DIM, typename T, int PF>
 __device__ __forceinline__ void elem_plap_gauss_vjp(const T *w, const T *lam, const Phys &ph, T h, T *r) {
     constexpr int NV = Cell<DIM>::NV, NH = NV / 2;
     T G[DIM][NH], L[DIM][NH];
@@ -247,8 +247,8 @@ __device__ __forceinline__ void elem_plap_gauss_vjp(const T *w, const T *lam, co
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         const T b = d2 + gq_dot<DIM, T>(G, G, q) * ih2;
-        k[q] = plap_pow<T>(b, ph.a0, 0);
-        cm[q] = T(ph.a0 - 2.0) * plap_pow<T>(b, ph.a0, 2) * gq_dot<DIM, T>(G, L, q) * ih2;
+        k[q] = plap_pow<T, PF>(b, ph.a0, 0);
+        cm[q] = T(ph.a0 - 2.0) * plap_pow<T, PF>(b, ph.a0, 2) * gq_dot<DIM, T>(G, L, q) * ih2;
     }
     T F[DIM][NH];
 #pragma unroll
@@ -458,11 +458,11 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
 }
 
 // Exact J_e^T lam (= J_e lam for the symmetric kinds), FP64 use.
-template <int DIM, int KIND, typename T>
+template <int DIM, int KIND, typename T, int PF = 0>
 __device__ __forceinline__ void elem_scalar_vjp(const T *w, const T *kap, const T *lam, const Phys &ph,
                                                 T h, T *r) {
     if constexpr (KIND == JFNK_PLAP_GAUSS) {
-        elem_plap_gauss_vjp<DIM, T>(w, lam, ph, h, r);
+        elem_plap_gauss_vjp<DIM, T, PF>(w, lam, ph, h, r);
         return;
     }
     constexpr int NV = Cell<DIM>::NV;
@@ -501,10 +501,10 @@ __device__ __forceinline__ void elem_scalar_vjp(const T *w, const T *kap, const 
         for (int a = 0; a < NV; ++a) { quad += w[a] * Ku[a]; kul += lam[a] * Ku[a]; }
         T s = quad / (h * h);
         T d2 = T(ph.a1) * T(ph.a1);
-        T k = plap_pow<T>(d2 + s, ph.a0, 0) * hs;
+        T k = plap_pow<T, PF>(d2 + s, ph.a0, 0) * hs;
         // (p-2)(delta^2+s)^((p-4)/2) / |e| * (K_e u)(K_e u)^T lam, K_e = hs K
         T vol = (DIM == 3) ? h * h * h : h * h;
-        T dk = T(ph.a0 - 2.0) * plap_pow<T>(d2 + s, ph.a0, 2) / vol * hs * hs * kul;
+        T dk = T(ph.a0 - 2.0) * plap_pow<T, PF>(d2 + s, ph.a0, 2) / vol * hs * hs * kul;
 #pragma unroll
         for (int a = 0; a < NV; ++a) r[a] = k * Kl[a] + dk * Ku[a];
         return;

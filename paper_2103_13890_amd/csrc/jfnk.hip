@@ -637,9 +637,9 @@ template <typename T> jfnk_status apply_op(jfnk_ctx *c, OpKind op, const T *z, c
     } else {
         if (!std::is_same<T, double>::value) {
             vec_cast<T, double>(c->ex, g, c->nc, z, c->tmpA, nullptr);
-            op_vjp(c->ex, g, c->ph, c->kap64, c->u, c->tmpA, 0, w);
+            ops<double>(c->ph).vjp(c->ex, g, c->ph, c->kap64, c->u, c->tmpA, w);
         } else {
-            op_vjp(c->ex, g, c->ph, c->kap64, c->u, (const double *)z, 0, w);
+            ops<double>(c->ph).vjp(c->ex, g, c->ph, c->kap64, c->u, (const double *)z, w);
         }
     }
     return check_launch(c);
@@ -1525,7 +1525,8 @@ jfnk_status jfnk_vjp(jfnk_ctx *c, int level, int wrt, const double *u, const dou
     if (c->prob.kind == JFNK_INVCOEF && !coef) return fail(c, JFNK_E_INVAL, "INVCOEF needs coef");
     const Grid &g = c->lev[level].g;
     const double *k = coef_kap<double>(c, level, coef, c->tmpB);
-    op_vjp(c->ex, g, c->ph, k, u, lam, wrt, out);
+    if (wrt == 0) ops<double>(c->ph).vjp(c->ex, g, c->ph, k, u, lam, out);
+    else ops<double>(c->ph).vjp_coef(c->ex, g, c->ph, k, u, lam, 1.0, out);
     return check_launch(c);
 }
 
@@ -1569,7 +1570,7 @@ jfnk_status jfnk_coef_gradient(jfnk_ctx *c, const double *u, const double *coef,
     if (!u || !coef || !lam || !grad) return fail(c, JFNK_E_INVAL, "null u, coef, lam or grad");
     const Grid &g = c->lev[c->L].g;
     const double *k = coef_kap<double>(c, c->L, coef, c->tmpB);
-    op_vjp(c->ex, g, c->ph, k, u, lam, 1, grad, -1.0);
+    ops<double>(c->ph).vjp_coef(c->ex, g, c->ph, k, u, lam, -1.0, grad);
     return check_launch(c);
 }
 

@@ -129,8 +129,11 @@ template <typename T> struct StencilTable {
                   const T *v, const double *num, const double *vn2, T *q, double *out);
     void (*jv_mixed)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
                      const float *v, const double *num, const double *vn2, double eps_fixed, T *Jv);
-    // a13 (FP64): exact J(u)^T lam on the DoFs
+    // FP64: a13, exact J(u)^T lam on the DoFs; a14, scale (dF/dm)^T lam at every
+    // node (INVCOEF; -1 gives the coefficient gradient exactly)
     void (*vjp)(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *lam, T *out);
+    void (*vjp_coef)(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *lam, double scale,
+                     T *out);
 };
 template <typename T, int KIND> const StencilTable<T> *stencil_table();
 template <typename T> inline const StencilTable<T> &ops(const Phys &ph) {
@@ -151,9 +154,6 @@ inline void op_jv(const Exec &ex, int mode, const Grid &g, const Phys &ph, const
 
 // energy Psi_h(u) (element sum) -> out[0]   (FP64, variational kinds)
 void op_energy(const Exec &, const Grid &, const Phys &, const double *u, double *out);
-// exact VJP: out = scale J(u)^T lam (wrt 0) or scale (dF/dm)^T lam (wrt 1, kap = e^m)
-void op_vjp(const Exec &, const Grid &, const Phys &, const double *kap, const double *u, const double *lam,
-            int wrt, double *out, double scale = 1.0);
 
 // ---- vectors (n = nodes, nc components, SoA) ---------------------------------
 template <typename T> void vec_fill(const Exec &, T *x, long long n, T val);

@@ -6,6 +6,8 @@
 //        M_FD_PLAIN val = (A(x + eps v) - A(x)) / eps, A(x) read from a cache
 //        M_FD_DIFF  val = the same quotient summed from per-element
 //                   difference forms (elem_*_fd), no cache read
+//        M_VJP      val = J(x)^T v from the exact element Jacobians
+//        M_COEF     val = sum_e (1 + ubar^2) (v^T K u)_e / 2^d at every node
 //   epilogue        consumes val at node i: store F = val - b, store J v,
 //                   a fused Chebyshev step, a power-method step, ...
 //
@@ -79,6 +81,26 @@ template <typename T, int NC> struct EpiJv {
     __device__ __forceinline__ void node(const At &at, const T *val, bool dir, double *, const T *) const {
 #pragma unroll
         for (int c = 0; c < NC; ++c) at.st(Jv, c * nn, dir ? T(0) : val[c]);
+    }
+    __device__ void operator()(const double *) const {}
+    double *slot() const { return nullptr; }
+};
+
+// coefficient product: out = scale e^m val at every node (kap = e^m)
+template <typename T, int NC> struct EpiCoef {
+    static constexpr int NS = 0;
+    static constexpr int NCOMP = NC;
+    static constexpr int NIN = 1;
+    static constexpr int VIN = -1;
+    const T *kap;
+    T *out;
+    T scale;
+    template <bool SKIPV = false, class At> __device__ __forceinline__ void load(const At &at, T *in) const {
+        in[0] = at.ld(kap, 0);
+    }
+    template <class At>
+    __device__ __forceinline__ void node(const At &at, const T *val, bool, double *, const T *in) const {
+        at.st(out, 0, scale * (val[0] * in[0]));
     }
     __device__ void operator()(const double *) const {}
     double *slot() const { return nullptr; }
@@ -307,7 +329,18 @@ template <class E> __device__ __forceinline__ double fd_eps_prepare(const FdStep
 template <int DIM, int KIND, int MODE, typename T, int NC, int NV, int PF = 0>
 __device__ __forceinline__ void elem_eval(const T (*xe)[NV], const T (*ve)[NV], const T *kp, T eps,
                                           const Phys &ph, T h, T (*r)[NV], T m = T(1)) {
-    if constexpr (MODE == M_FD_DIFF) {
+    if constexpr (MODE == M_VJP || MODE == M_COEF) {
+        if constexpr (MODE == M_VJP) {
+            elem_scalar_vjp<DIM, KIND, T, PF>(xe[0], kp, ve[0], ph, h, r[0]);
+        } else {
+            const T f = elem_coef_factor<DIM, T>(xe[0], ve[0], h);
+#pragma unroll
+            for (int a = 0; a < NV; ++a) r[0][a] = f;
+        }
+        const bool on = m != T(0);
+#pragma unroll
+        for (int a = 0; a < NV; ++a) r[0][a] = on ? r[0][a] : T(0);
+    } else if constexpr (MODE == M_FD_DIFF) {
         elem_scalar_fd<DIM, KIND, T, PF>(xe[0], ve[0], kp, eps, ph, h, r[0], m);
     } else if constexpr (MODE == M_FD_PLAIN) {
         T w[NV];
@@ -331,7 +364,8 @@ __device__ __forceinline__ void node_value_scalar(const Grid &g, const Phys &ph,
     constexpr int NV = Cell<DIM>::NV;
     constexpr int NZ3 = DIM == 3 ? 3 : 1;
     constexpr int NB = 9 * NZ3;
-    constexpr bool FD = MODE != M_RESID;
+    constexpr bool DIR = MODE != M_RESID;
+    constexpr bool FD = MODE == M_FD_PLAIN || MODE == M_FD_DIFF;
     constexpr bool INV = KIND == JFNK_INVCOEF;
     val[0] = T(0);
     if (FD && eps == 0.0) return;
@@ -357,9 +391,9 @@ __device__ __forceinline__ void node_value_scalar(const Grid &g, const Phys &ph,
                 const long long j = node_index(g, ax, ay, az);
                 const bool in = ok[0][dx] && ok[1][dy] && ok[2][DIM == 3 ? dz : 1];
                 nx[k] = x[j];
-                nv[k] = FD ? (T)v[j] : T(0);
+                nv[k] = DIR ? (T)v[j] : T(0);
                 nk[k] = INV ? kap[j] : T(0);
-                if (FD && (!in || is_dirichlet(g, ax, ay, az))) nv[k] = T(0);
+                if (DIR && (!in || is_dirichlet(g, ax, ay, az))) nv[k] = T(0);
                 if (!in) { nx[k] = T(0); nk[k] = T(0); }
             }
 #pragma unroll
@@ -395,7 +429,7 @@ __global__ __launch_bounds__(BLOCK) void k_node(Grid g, Phys ph, const T *kap, c
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < g.nn; i += stride) {
         int X, Y, Z;
         node_coords(g, i, X, Y, Z);
-        const bool dir = is_dirichlet(g, X, Y, Z);
+        const bool dir = MODE != M_COEF && is_dirichlet(g, X, Y, Z);
         T val[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) val[c] = T(0);
@@ -414,7 +448,8 @@ template <int DIM, int KIND, int MODE, typename T, typename TV>
 __device__ __forceinline__ T node_elem_scalar(const Grid &g, const Phys &ph, const T *kap, const T *x, const TV *v,
                                               double eps, int X, int Y, int Z, int el) {
     constexpr int NV = Cell<DIM>::NV;
-    constexpr bool FD = MODE != M_RESID;
+    constexpr bool DIR = MODE != M_RESID;
+    constexpr bool FD = MODE == M_FD_PLAIN || MODE == M_FD_DIFF;
     constexpr bool INV = KIND == JFNK_INVCOEF;
     const int ex = X - (el & 1), ey = Y - ((el >> 1) & 1), ez = DIM == 3 ? Z - ((el >> 2) & 1) : 0;
     if (ex < 0 || ex >= g.nx || ey < 0 || ey >= g.ny) return T(0);
@@ -425,7 +460,7 @@ __device__ __forceinline__ T node_elem_scalar(const Grid &g, const Phys &ph, con
         const int ax = ex + (a & 1), ay = ey + ((a >> 1) & 1), az = ez + ((a >> 2) & 1);
         const long long j = node_index(g, ax, ay, az);
         xe[0][a] = x[j];
-        ve[0][a] = (FD && !is_dirichlet(g, ax, ay, az)) ? (T)v[j] : T(0);
+        ve[0][a] = (DIR && !is_dirichlet(g, ax, ay, az)) ? (T)v[j] : T(0);
         kp[a] = INV ? kap[j] : T(0);
     }
     elem_eval<DIM, KIND, MODE, T, 1, NV>(xe, ve, kp, (T)eps, ph, (T)g.h, r);
@@ -464,9 +499,10 @@ __global__ __launch_bounds__(BLOCK) void k_node_split(Grid g, Phys ph, const T *
         bool dir = true;
         if (live) {
             node_coords(g, i, X, Y, Z);
-            dir = is_dirichlet(g, X, Y, Z);
+            dir = MODE != M_COEF && is_dirichlet(g, X, Y, Z);
         }
-        const bool eval = live && !dir && !(MODE != M_RESID && eps == 0.0);
+        constexpr bool FDM = MODE == M_FD_PLAIN || MODE == M_FD_DIFF;
+        const bool eval = live && !dir && !(FDM && eps == 0.0);
         T c = T(0);
         if (eval) c = node_elem_scalar<DIM, KIND, MODE, T, TV>(g, ph, kap, x, v, eps, X, Y, Z, el);
 #pragma unroll

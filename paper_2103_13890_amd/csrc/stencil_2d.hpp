@@ -100,7 +100,7 @@ __global__ __launch_bounds__(BLOCK) void k_row2(Grid g, Phys ph, const T *kap, c
             if (r >= 1) {      // node row r - 1 of the tile is complete
                 const int Y = y0 + r - 1;
                 T val[1] = {(c0 + r4[0][0]) + from_left(c1 + r4[0][1])};
-                const bool dir = xdir || ydir(Y);
+                const bool dir = MODE != M_COEF && (xdir || ydir(Y));
                 if constexpr (PLAIN) val[0] = (val[0] - pax[r - 1]) * ie;
                 if (dir || zero_fd) val[0] = T(0);
                 if (own && Y <= g.ny) epi.node(PtrAt{(long long)Y * g.NX + X}, val, dir, sums, in[r - 1]);

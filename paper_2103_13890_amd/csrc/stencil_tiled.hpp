@@ -29,7 +29,9 @@ namespace jfnk {
 // FP32 4 (under 128 VGPRs, 4 waves per SIMD; faster than 3, 5, 6 or 8
 // despite the larger y halo); FP64: 4 for the plain FD quotient without
 // epilogue inputs (the outer J v: 166 VGPRs, 3 waves per SIMD, faster than
-// 6 rows at 2 waves), 3 for the residual (124 VGPRs, 4 waves per SIMD),
+// 6 rows at 2 waves), 3 for the residual (124 VGPRs, 4 waves per SIMD) and
+// the exact VJP (166 VGPRs, 3 waves, 39.1 us at 128^3 for the p-Laplacian
+// against 42.3 us with 4 rows at 2 waves; node-centric it took 190 us),
 // 4 otherwise.  The FP64 Gauss-point p-Laplacian takes 3 in every mode
 // (p = 3 instantiation: the residual at 136 VGPRs, 3 waves per SIMD, beats
 // 2 rows at 116 VGPRs and 4 waves, 346 against 379 us at 256^3; in the FD
@@ -39,7 +41,8 @@ template <typename T, int MODE, class Epi, int KIND> struct TileRows {
     static constexpr bool jv64 = sizeof(T) == 8 && MODE == M_FD_PLAIN && Epi::NIN == 0;
     static constexpr bool res64 = sizeof(T) == 8 && MODE == M_RESID;
     static constexpr bool gauss64 = sizeof(T) == 8 && KIND == JFNK_PLAP_GAUSS;
-    static constexpr int value = gauss64 ? GAUSS_ROWS64 : (jv64 ? 4 : (res64 ? 3 : 4));
+    static constexpr bool vjp64 = sizeof(T) == 8 && MODE == M_VJP;
+    static constexpr int value = vjp64 ? 3 : gauss64 ? GAUSS_ROWS64 : (jv64 ? 4 : (res64 ? 3 : 4));
 };
 constexpr int TMAX_THREADS = 512;   // nx <= 512 elements per row
 
@@ -56,21 +59,22 @@ __device__ __forceinline__ int xcd_tile(int id, int nb) {
 }
 
 // Dynamic LDS of one block: two plane slots of x (T), e^m (T, INVCOEF) and
-// v (TV, FD modes), plus the (tile rows) x pitch hand-over buffer (T).
+// v (TV, modes with a direction), plus the (tile rows) x pitch hand-over buffer (T).
 template <typename T, typename TV, int MODE, class Epi, int KIND>
 inline size_t tiled_lds_bytes(int pitch, int srows) {
-    constexpr bool FD = MODE != M_RESID;
+    constexpr bool DIR = MODE != M_RESID;
     constexpr bool INV = KIND == JFNK_INVCOEF;
     const size_t plane = (size_t)srows * pitch;
     return 2 * plane * sizeof(T) * (INV ? 2 : 1) + (size_t)TileRows<T, MODE, Epi, KIND>::value * pitch * sizeof(T) +
-           (FD ? 2 * plane * sizeof(TV) : 0);
+           (DIR ? 2 * plane * sizeof(TV) : 0);
 }
 
 // PF = 3: p-Laplacian with p = 3 fixed at compile time (no exponent branches)
 template <int KIND, int MODE, typename T, typename TV, class Epi, int PF = 0>
 __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T *kap, const T *x, const TV *v,
                                                         const T *Ax, FdStep fd, Epi epi, Red red, TileArgs ta) {
-    constexpr bool FD = MODE != M_RESID;
+    constexpr bool DIR = MODE != M_RESID;                            // has a direction v
+    constexpr bool FD = MODE == M_FD_PLAIN || MODE == M_FD_DIFF;     // with a step eps
     constexpr bool INV = KIND == JFNK_INVCOEF;
     constexpr int R = TileRows<T, MODE, Epi, KIND>::value;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
     T *sx = (T *)smem;                            // [2][plane]
     T *sk = sx + 2 * plane;                       // [2][plane] (INVCOEF)
     T *xb = sk + (INV ? 2 * plane : 0);           // [R][P] hand-over rows
-    TV *sv = (TV *)(xb + R * P);                  // [2][plane] (FD)
+    TV *sv = (TV *)(xb + R * P);                  // [2][plane] (DIR)
 
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int tiy = tile % ta.nty, tiz = tile / ta.nty;
@@ -164,7 +168,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
     // inputs in flight across the element work the FP32 Chebyshev step at
     // 256^3 took 148 us instead of 136 us (150 us with the fetch spread over
     // the element rows).
-    constexpr bool LATE = !FD;
+    constexpr bool LATE = !DIR;
     const int tc = t < uNX ? t : uNX - 1;
     T px[R + 2], pk[R + 2], qx = T(0), qk = T(0);
     TV pv[R + 2], qv = TV(0);
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
             const int gyc = gy < 0 ? 0 : (gy >= uNY ? uNY - 1 : gy);
             const BufAt at{(unsigned)((pzc * uNY + gyc) * uNX), (unsigned)tc};
             px[r] = at.ld(x, 0);
-            if constexpr (FD) {
+            if constexpr (DIR) {
                 const TV vv = at.ld(v, 0);
                 pv[r] = (zfree && ((ufree >> r) & 1u)) ? vv * vlane : TV(0);
             }
@@ -196,7 +200,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
             } else {
                 qx = in ? xv : T(0);
             }
-            if constexpr (FD) {
+            if constexpr (DIR) {
                 const TV vv = v[idx];
                 qv = (in && !(xdir_e || zd || ydir_u(gy))) ? vv : TV(0);
             }
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
             for (int r = 0; r < R + 2; ++r) {
                 if (r < usrows) {
                     sx[sl * plane + r * P + t] = px[r];
-                    if constexpr (FD) sv[sl * plane + r * P + t] = pv[r];
+                    if constexpr (DIR) sv[sl * plane + r * P + t] = pv[r];
                     if constexpr (INV) sk[sl * plane + r * P + t] = pk[r];
                 }
             }
@@ -241,7 +245,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
                 in = pz >= 0 && pz < uNZ && gy >= 0 && gy < uNY && t < urows + 2;
             }
             sx[sl * plane + t * P + unx] = in ? qx : T(0);
-            if constexpr (FD) sv[sl * plane + t * P + unx] = qv;
+            if constexpr (DIR) sv[sl * plane + t * P + unx] = qv;
             if constexpr (INV) sk[sl * plane + t * P + unx] = in ? qk : T(0);
         }
     };
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
         auto row = [&](int r, T(&ox)[4], TV(&ov)[4], T(&ok)[4]) {
             const int o = (r < usrows ? r : usrows - 1) * P;
             ox[0] = sx[lo + o]; ox[1] = sx[lo + o + 1]; ox[2] = sx[hi + o]; ox[3] = sx[hi + o + 1];
-            if constexpr (FD) { ov[0] = sv[lo + o]; ov[1] = sv[lo + o + 1]; ov[2] = sv[hi + o]; ov[3] = sv[hi + o + 1]; }
+            if constexpr (DIR) { ov[0] = sv[lo + o]; ov[1] = sv[lo + o + 1]; ov[2] = sv[hi + o]; ov[3] = sv[hi + o + 1]; }
             if constexpr (INV) { ok[0] = sk[lo + o]; ok[1] = sk[lo + o + 1]; ok[2] = sk[hi + o]; ok[3] = sk[hi + o + 1]; }
         };
         if (lz) row(0, cx, cv, ck);
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
         for (int q = t; q < 2 * ta.srows * pad; q += nthr) {
             const int o = (q / pad) * P + g.NX + q % pad;
             sx[o] = T(0);
-            if constexpr (FD) sv[o] = TV(0);
+            if constexpr (DIR) sv[o] = TV(0);
             if constexpr (INV) sk[o] = T(0);
         }
     }
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
     // (nx, y0 + k) of the last column is finished by thread k.
     constexpr int NIN = Epi::NIN > 0 ? Epi::NIN : 1;
     constexpr bool PLAIN = MODE == M_FD_PLAIN;
-    constexpr bool VLDS = FD && Epi::VIN >= 0 && Epi::NCOMP == 1;
+    constexpr bool VLDS = DIR && Epi::VIN >= 0 && Epi::NCOMP == 1;
     for (int z = z0; z < z1; ++z) {
         refresh();
         T pin[R][NIN], pax[R], qin[NIN], qax = T(0);
@@ -394,7 +398,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
                 const int gy = uy0 + k;
                 if (own_col && k < urows) {
                     const BufAt at{(unsigned)((z * uNY + gy) * uNX), (unsigned)t};
-                    const bool dir = zd || ((uodir >> k) & 1u) || xdir_t;
+                    const bool dir = MODE != M_COEF && (zd || ((uodir >> k) & 1u) || xdir_t);
                     T val[1] = {T(0)};
                     if (!dir && !zero_fd) {
                         T acc = O[k] + xb[k * P + t];
@@ -407,7 +411,7 @@ __global__ __launch_bounds__(TMAX_THREADS) void k_tiled(Grid g, Phys ph, const T
             if (extra && t < urows) {
                 const int gy = uy0 + t;
                 const PtrAt at{(long long)((z * uNY + gy) * uNX + unx)};
-                const bool dir = zd || ydir_u(gy) || xdir_e;
+                const bool dir = MODE != M_COEF && (zd || ydir_u(gy) || xdir_e);
                 T val[1] = {T(0)};
                 if (!dir && !zero_fd) {
                     T acc = xb[t * P + unx];
