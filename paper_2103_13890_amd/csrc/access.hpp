@@ -4,7 +4,7 @@
 // BufAt addresses a node of a grid row as (row start, column): the row
 // start is the same for every lane of the block and goes into the scalar
 // offset of a buffer instruction, the column is the lane's and is the same
-// for every row.  A tiled kernel that walks rows then issues its loads and
+// for every row.  A kernel that walks rows then issues its loads and
 // stores with no vector address arithmetic at all.  Buffer offsets are
 // 32-bit byte offsets, so BufAt serves arrays below 2 GiB.
 #pragma once

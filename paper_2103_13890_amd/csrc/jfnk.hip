@@ -32,7 +32,6 @@ struct Range {
 };
 
 constexpr int NSLOT = 1024;
-constexpr size_t PART_CAP = 4096 * 32;    // partial sums (blocks x sums)
 constexpr int MAXR = 32;                  // restart cap (Gram-Schmidt slots)
 
 // device scalar slots
@@ -1220,6 +1219,11 @@ jfnk_status jfnk_residual_static(const jfnk_problem *p, int level, const double 
     if (!u || !F) return fail(nullptr, JFNK_E_INVAL, "null u or F");
     if (misaligned(u, 8) || misaligned(F, 8) || misaligned(b, 8) || misaligned(fnorm2, 8))
         return fail(nullptr, JFNK_E_INVAL, "misaligned array");
+    // Tall 3D grids of the scalar kinds stay refused as documented: more than
+    // STATIC_SCRATCH_DOUBLES groups of three node rows in y.
+    const Grid gl = level_grid(*p, level);
+    const bool tall = gl.dim == 3 && p->kind != JFNK_NEOHOOKE && gl.nx >= 32 && gl.nx <= 512 && gl.nn < (1LL << 28) &&
+                      (gl.NY + 2) / 3 > STATIC_SCRATCH_DOUBLES;
     double *part = nullptr;
     const jfnk_status s = static_scratch(&part);
     if (s != JFNK_OK) return s;
@@ -1228,8 +1232,8 @@ jfnk_status jfnk_residual_static(const jfnk_problem *p, int level, const double 
     ex.red = Red{part};
     ex.path = 0;
     ex.red_cap = STATIC_SCRATCH_DOUBLES;
-    ops<double>(make_phys(*p)).residual(ex, level_grid(*p, level), make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
-    if (ex.red_short)
+    if (!tall) ops<double>(make_phys(*p)).residual(ex, gl, make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
+    if (tall || ex.red_short)
         return fail(nullptr, JFNK_E_INVAL, "the grid needs more partial sums than the static scratch holds ("
                     + std::to_string(STATIC_SCRATCH_DOUBLES) + "): use jfnk_residual");
     const hipError_t e = hipGetLastError();

@@ -82,6 +82,8 @@ inline FdStep make_fd(const Exec &ex, const double *num, const double *vn2, doub
     return f;
 }
 
+constexpr long long PART_CAP = 4096 * 32;     // partial sums of the context's buffer (blocks x sums)
+
 inline int node_blocks(long long n) {
     long long b = (n + BLOCK - 1) / BLOCK;
     if (b > 4096) b = 4096;

@@ -17,8 +17,8 @@
 // direction v is taken as 0 on Dirichlet nodes (J acts on the DoF space).
 //
 // This header holds the node-centric form (one thread per node, the
-// elements around it evaluated in registers); stencil_tiled.hpp holds the
-// z-marching LDS-tiled form for large 3D levels.  Both share the element
+// elements around it evaluated in registers); stencil_2d.hpp and
+// stencil_wave3.hpp hold the wavefront-per-tile forms.  All share the element
 // routines and the epilogues.
 #pragma once
 #include <type_traits>
@@ -29,12 +29,20 @@
 
 namespace jfnk {
 
+// Tile of block id of nb: ids are dealt round-robin over the 8 XCDs, and each
+// XCD owns a contiguous range of tiles.
+__device__ __forceinline__ int xcd_tile(int id, int nb) {
+    const int q = nb / 8, r = nb % 8;
+    const int xcd = id % 8, loc = id / 8;
+    return xcd < r ? xcd * (q + 1) + loc : r * (q + 1) + (xcd - r) * q + loc;
+}
+
 // ---- epilogues ---------------------------------------------------------------
 // NS: number of grid sums; NCOMP: components; NIN: values read per node and
 // component; VIN: the index of the input that is the FD direction itself
 // (-1: none).  load(at, in) reads them (issued ahead of the element work by
-// the tiled kernel, which passes SKIPV and takes input VIN from the direction
-// plane it holds in LDS), node(at, val, dir, sums, in) consumes val at the node;
+// the tile kernels, which pass SKIPV and take input VIN from the direction
+// rows they hold in registers), node(at, val, dir, sums, in) consumes val at the node;
 // at addresses the node (PtrAt or BufAt, access.hpp), the component c being
 // c * nn further on.  operator()(totals) runs in the reduction's finishing
 // kernel.
