@@ -26,17 +26,6 @@ constexpr double GL1 = 0.78867513459481288225;   // 1/2 + 1/(2 sqrt 3)
 
 template <int DIM> struct Cell { static constexpr int NV = 1 << DIM; };
 
-// phi_b at Gauss point q: GL1^(DIM-c) GL0^c with c = popcount(b ^ q).
-template <int DIM, typename T>
-__device__ __forceinline__ T phi_gauss(int c) {
-    if (DIM == 2) {
-        return c == 0 ? T(GL1 * GL1) : (c == 1 ? T(GL1 * GL0) : T(GL0 * GL0));
-    } else {
-        return c == 0 ? T(GL1 * GL1 * GL1)
-                      : (c == 1 ? T(GL1 * GL1 * GL0) : (c == 2 ? T(GL1 * GL0 * GL0) : T(GL0 * GL0 * GL0)));
-    }
-}
-
 // (K u)_a for all corners (without the h^(d-2) factor).
 template <int DIM, typename T>
 __device__ __forceinline__ void stiff_apply(const T *u, T *Ku) {
@@ -68,6 +57,47 @@ __device__ __forceinline__ void stiff_apply_s(const T *u, T *Ku) {
             const T far = (u[a ^ 3] + u[a ^ 5]) + (u[a ^ 6] + u[a ^ 7]);
             Ku[a] = T(4) * u[a] - far;
         }
+    }
+}
+
+// Values of a Q1 field at the tensor Gauss points from its corner values, axis
+// by axis (three operations per pair).  The operator is symmetric: it also
+// sums Gauss-point values against the basis functions at the corners.
+template <int DIM, typename T> __device__ __forceinline__ void gauss_interp(const T *u, T *uq) {
+#pragma unroll
+    for (int a = 0; a < (1 << DIM); ++a) uq[a] = u[a];
+#pragma unroll
+    for (int k = 0; k < DIM; ++k)
+#pragma unroll
+        for (int a = 0; a < (1 << DIM); ++a)
+            if (!((a >> k) & 1)) {
+                const int b = a | (1 << k);
+                const T t = T(GL0) * (uq[b] - uq[a]);
+                uq[a] += t;
+                uq[b] -= t;
+            }
+}
+
+// (e^{eps v} - 1) / eps at NV points.  The FD steps make eps v small: below
+// 2^-10 everywhere, the Taylor series of (e^y - 1)/y (its first omitted term is
+// under 2^-59 in FP64, 2^-34 in FP32, where it is cut earlier) replaces expm1,
+// which takes about as long as the exponential itself.
+template <int NV, typename T> __device__ __forceinline__ void expm1_quot(const T *v, T eps, T *q) {
+    T big = T(0);
+#pragma unroll
+    for (int a = 0; a < NV; ++a) big = fmax(big, fabs(v[a]));
+    if (eps * big < T(1.0 / 1024.0)) {
+#pragma unroll
+        for (int a = 0; a < NV; ++a) {
+            const T y = eps * v[a];
+            T s = T(1.0 / 6.0);
+            if (sizeof(T) == 8) s += y * (T(1.0 / 24.0) + y * T(1.0 / 120.0));
+            q[a] = v[a] + v[a] * (y * (T(0.5) + y * s));
+        }
+    } else {
+        const T ie = T(1) / eps;
+#pragma unroll
+        for (int a = 0; a < NV; ++a) q[a] = expm1(eps * v[a]) * ie;
     }
 }
 
@@ -113,18 +143,7 @@ template <int DIM> __device__ __forceinline__ constexpr int gq_other(int i, int 
     return ((q >> (i == 0 ? 1 : 0)) & 1) | (((q >> (i == 2 ? 1 : 2)) & 1) << 1);
 }
 template <int DIM, typename T> __device__ __forceinline__ void gq_interp(const T *in, T *out) {
-    const T A = T(GL1), B = T(GL0);
-    if (DIM == 2) {
-        out[0] = A * in[0] + B * in[1];
-        out[1] = B * in[0] + A * in[1];
-    } else {
-        const T t0 = A * in[0] + B * in[1], t1 = B * in[0] + A * in[1];
-        const T t2 = A * in[2] + B * in[3], t3 = B * in[2] + A * in[3];
-        out[0] = A * t0 + B * t2;
-        out[1] = A * t1 + B * t3;
-        out[2] = B * t0 + A * t2;
-        out[3] = B * t1 + A * t3;
-    }
+    gauss_interp<DIM - 1, T>(in, out);
 }
 template <int DIM, typename T> __device__ __forceinline__ void gq_grad(const T *u, T (*G)[1 << (DIM - 1)]) {
     constexpr int NH = 1 << (DIM - 1);
@@ -168,6 +187,45 @@ template <int DIM, typename T> __device__ __forceinline__ T gq_pair(const T *k, 
     return k[gq_corner<DIM>(i, 0, j)] + k[gq_corner<DIM>(i, 1, j)];
 }
 
+// k_w = b_w^al, al = (p-2)/2, and dk = (k_w - k_x) / eps from b_x and
+// dsq = (b_w - b_x) / eps, without the cancellation of the difference.  For
+// p = 3 and 1 by roots.  For other exponents the FD steps make the relative
+// change u = eps dsq / b_x tiny, and the binomial series of
+// ((1 + u)^al - 1) / u, whose first omitted term is under 2^-54 in FP64 (2^-26
+// in FP32) at the limit taken here, replaces log1p and expm1, which take longer
+// than the power itself (a degree-4 smoother, p = 2.5, 128^3: FP64 306 -> 241
+// us, FP32 145 -> 110 us); beyond the limit (also b_x = 0, infinities, NaN) the
+// closed form.  For p = 3 and 1 the series was no faster, and the registers of
+// its two branches cost the FP64 Gauss-point element half its waves.
+template <typename T, int PF>
+__device__ __forceinline__ void plap_pair(T bx, T dsq, T eps, double p, T &kw, T &dk) {
+    const T bw = bx + eps * dsq;
+    if (PF == 3 || (PF == 0 && p == 3.0)) {
+        const T kx = hw_sqrt(bx);
+        kw = hw_sqrt(bw);
+        dk = hw_div(dsq, kw + kx);
+    } else if (PF == 0 && p == 2.0) {
+        kw = T(1);
+        dk = T(0);
+    } else if (PF == 1 || p == 1.0) {   // the minimal surface, k = b^(-1/2):
+        // (k_w - k_x) / eps = -dsq / (s_x s_w (s_x + s_w)), s = sqrt(b)
+        const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
+        kw = hw_div(T(1), sw);
+        dk = -hw_div(dsq, sx * sw * (sx + sw));
+    } else {
+        const T al = T(0.5 * (p - 2.0)), kx = (T)pow(bx, al), s = dsq / bx, u = eps * s;
+        if (fabs(u) * (fabs(al) + T(4)) < T(sizeof(T) == 8 ? 0x1p-12 : 0x1p-5)) {
+            const T c1 = (al - T(1)) * T(0.5), c2 = (al - T(2)) * T(1.0 / 3.0), c3 = (al - T(3)) * T(0.25);
+            dk = kx * al * s * (T(1) + c1 * u * (T(1) + c2 * u * (T(1) + c3 * u)));
+            kw = kx + eps * dk;
+        } else {
+            const T em = expm1(al * log1p(u));
+            kw = kx * (T(1) + em);
+            dk = kx * em / eps;
+        }
+    }
+}
+
 // PLAP_GAUSS element vector; c = m |e| / (2^d h^2) (= m h^(d-2) / 2^d)
 template <int DIM, typename T, int PF>
 __device__ __forceinline__ void elem_plap_gauss(const T *w, const Phys &ph, T h, T *r, T m) {
@@ -188,47 +246,37 @@ __device__ __forceinline__ void elem_plap_gauss(const T *w, const Phys &ph, T h,
     gq_scatter<DIM, T>(F, on ? m * hs * T(1.0 / NV) : T(0), r);
 }
 
-// PLAP_GAUSS FD quotient in difference form: per Gauss point
-// k_w - k_x from s_w - s_x = eps (2 g_x . g_v + eps |g_v|^2), as for PLAP
+// PLAP_GAUSS FD quotient in difference form: per Gauss point, with the mean
+// gradient g = g_x + eps/2 g_v and the mean coefficient k = (k_x + k_w)/2, the
+// flux quotient (k_w g_w - k_x g_x) / eps = k g_v + (k_w - k_x)/eps g, and
+// s_w - s_x = 2 eps g . g_v
 template <int DIM, typename T, int PF>
 __device__ __forceinline__ void elem_plap_gauss_fd(const T *x, const T *v, T eps, const Phys &ph, T h, T *q_out,
                                                    T m) {
     constexpr int NV = Cell<DIM>::NV, NH = NV / 2;
-    T Gx[DIM][NH], Gv[DIM][NH];
-    gq_grad<DIM, T>(x, Gx);
+    T G[DIM][NH], Gv[DIM][NH];
+    gq_grad<DIM, T>(x, G);
     gq_grad<DIM, T>(v, Gv);
-    const T ih2 = T(1) / (h * h), d2 = T(ph.a1) * T(ph.a1);
-    T kw[NV], dk[NV];
+    const T ih2 = T(1) / (h * h), d2 = T(ph.a1) * T(ph.a1), e2 = T(0.5) * eps;
+    T k[NV], dk[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) k[q] = d2 + gq_dot<DIM, T>(G, G, q) * ih2;
+#pragma unroll
+    for (int i = 0; i < DIM; ++i)
+#pragma unroll
+        for (int j = 0; j < NH; ++j) G[i][j] += e2 * Gv[i][j];
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
-        const T bx = d2 + gq_dot<DIM, T>(Gx, Gx, q) * ih2;
-        const T dsq = (T(2) * gq_dot<DIM, T>(Gx, Gv, q) + eps * gq_dot<DIM, T>(Gv, Gv, q)) * ih2;
-        const T bw = bx + eps * dsq;
-        if (PF == 3 || (PF == 0 && ph.a0 == 3.0)) {
-            const T kx = hw_sqrt(bx);
-            kw[q] = hw_sqrt(bw);
-            dk[q] = hw_div(dsq, kw[q] + kx);
-        } else if (PF == 0 && ph.a0 == 2.0) {
-            kw[q] = T(1);
-            dk[q] = T(0);
-        } else if (PF == 1 || ph.a0 == 1.0) {   // k = b^(-1/2): (k_w - k_x)/eps = -dsq / (s_x s_w (s_x + s_w))
-            const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
-            kw[q] = hw_div(T(1), sw);
-            dk[q] = -hw_div(dsq, sx * sw * (sx + sw));
-        } else {
-            const T al = T(0.5 * (ph.a0 - 2.0));
-            const T kx = (T)pow(bx, al);
-            const T em = expm1(al * log1p(eps * dsq / bx));
-            kw[q] = kx * (T(1) + em);
-            dk[q] = kx * em / eps;
-        }
+        T kw;
+        plap_pair<T, PF>(k[q], T(2) * ih2 * gq_dot<DIM, T>(G, Gv, q), eps, ph.a0, kw, dk[q]);
+        k[q] = kw - e2 * dk[q];
     }
     T F[DIM][NH];
 #pragma unroll
     for (int i = 0; i < DIM; ++i)
 #pragma unroll
         for (int j = 0; j < NH; ++j)
-            F[i][j] = Gv[i][j] * gq_pair<DIM, T>(kw, i, j) + Gx[i][j] * gq_pair<DIM, T>(dk, i, j);
+            F[i][j] = Gv[i][j] * gq_pair<DIM, T>(k, i, j) + G[i][j] * gq_pair<DIM, T>(dk, i, j);
     const T hs = (DIM == 3) ? h : T(1);
     const bool on = m != T(0);
     gq_scatter<DIM, T>(F, on ? m * hs * T(1.0 / NV) : T(0), q_out);
@@ -282,18 +330,11 @@ __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys
     if (KIND == JFNK_BRATU) {
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
-        T src[NV];
+        T uq[NV], src[NV];
+        gauss_interp<DIM, T>(w, uq);
 #pragma unroll
-        for (int a = 0; a < NV; ++a) src[a] = T(0);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            T uq = T(0);
-#pragma unroll
-            for (int b = 0; b < NV; ++b) uq += phi_gauss<DIM, T>(__builtin_popcount(b ^ q)) * w[b];
-            T e = exp(uq);
-#pragma unroll
-            for (int a = 0; a < NV; ++a) src[a] += e * phi_gauss<DIM, T>(__builtin_popcount(a ^ q));
-        }
+        for (int q = 0; q < NV; ++q) uq[q] = exp(uq[q]);
+        gauss_interp<DIM, T>(uq, src);
         T lw = T(ph.a0) * wq * m;
 #pragma unroll
         for (int a = 0; a < NV; ++a) r[a] = hk * Ku[a] - lw * src[a];
@@ -342,14 +383,10 @@ __device__ __forceinline__ T elem_scalar_energy(const T *w, const Phys &ph, T h)
     for (int a = 0; a < NV; ++a) quad += w[a] * Ku[a];
     T vol = (DIM == 3) ? h * h * h : h * h;
     if (KIND == JFNK_BRATU) {
-        T acc = T(0);
+        T uq[NV], acc = T(0);
+        gauss_interp<DIM, T>(w, uq);
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            T uq = T(0);
-#pragma unroll
-            for (int b = 0; b < NV; ++b) uq += phi_gauss<DIM, T>(__builtin_popcount(b ^ q)) * w[b];
-            acc += exp(uq);
-        }
+        for (int q = 0; q < NV; ++q) acc += exp(uq[q]);
         return T(0.5) * hs * quad - T(ph.a0) * (vol / T(NV)) * acc;
     }
     // PLAP: |e|/p (delta^2 + s)^(p/2)
@@ -385,23 +422,13 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
         // sum_q w_q (e^{w_q} - e^{x_q}) phi_a / eps = sum_q w_q e^{x_q} expm1(eps v_q) / eps phi_a
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
-        T src[NV];
+        T xq[NV], vq[NV], dq[NV], src[NV];
+        gauss_interp<DIM, T>(x, xq);
+        gauss_interp<DIM, T>(v, vq);
+        expm1_quot<NV, T>(vq, eps, dq);
 #pragma unroll
-        for (int a = 0; a < NV; ++a) src[a] = T(0);
-        const T ie = T(1) / eps;
-#pragma unroll
-        for (int qq = 0; qq < NV; ++qq) {
-            T xq = T(0), vq = T(0);
-#pragma unroll
-            for (int b = 0; b < NV; ++b) {
-                const T f = phi_gauss<DIM, T>(__builtin_popcount(b ^ qq));
-                xq += f * x[b];
-                vq += f * v[b];
-            }
-            const T e = exp(xq) * (expm1(eps * vq) * ie);
-#pragma unroll
-            for (int a = 0; a < NV; ++a) src[a] += e * phi_gauss<DIM, T>(__builtin_popcount(a ^ qq));
-        }
+        for (int a = 0; a < NV; ++a) dq[a] *= exp(xq[a]);
+        gauss_interp<DIM, T>(dq, src);
         const T lw = T(ph.a0) * wq * m;
 #pragma unroll
         for (int a = 0; a < NV; ++a) q[a] = hk * Kv[a] - lw * src[a];
@@ -421,27 +448,7 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
         const T ih2 = T(1) / (T(KS) * h * h);
         const T bx = T(ph.a1) * T(ph.a1) + qxx * ih2;
         const T dsq = (T(2) * qxv + eps * qvv) * ih2;        // (s_w - s_x) / eps
-        const T bw = bx + eps * dsq;
-        if (PF == 3 || (PF == 0 && ph.a0 == 3.0)) {
-            const T kx = hw_sqrt(bx);
-            kw = hw_sqrt(bw);
-            dk = hw_div(dsq, kw + kx);
-        } else if (PF == 0 && ph.a0 == 2.0) {
-            kw = T(1);
-            dk = T(0);
-        } else if (PF == 1 || ph.a0 == 1.0) {   // the minimal surface, k = b^(-1/2):
-            // (k_w - k_x) / eps = -dsq / (s_x s_w (s_x + s_w)), s = sqrt(b)
-            const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
-            kw = hw_div(T(1), sw);
-            dk = -hw_div(dsq, sx * sw * (sx + sw));
-        } else {
-            const T al = T(0.5 * (ph.a0 - 2.0));
-            const T kx = (T)pow(bx, al);
-            const T t = eps * dsq / bx;
-            const T em = expm1(al * log1p(t));
-            kw = kx * (T(1) + em);
-            dk = kx * em / eps;
-        }
+        plap_pair<T, PF>(bx, dsq, eps, ph.a0, kw, dk);
     } else {   // INVCOEF: k = kbar (1 + ubar^2)
         T ks = T(0), xs = T(0), vs = T(0);
 #pragma unroll
@@ -472,22 +479,12 @@ __device__ __forceinline__ void elem_scalar_vjp(const T *w, const T *kap, const 
     if (KIND == JFNK_BRATU) {
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
-        T src[NV];
+        T uq[NV], lq[NV], src[NV];
+        gauss_interp<DIM, T>(w, uq);
+        gauss_interp<DIM, T>(lam, lq);
 #pragma unroll
-        for (int a = 0; a < NV; ++a) src[a] = T(0);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            T uq = T(0), lq = T(0);
-#pragma unroll
-            for (int b = 0; b < NV; ++b) {
-                T f = phi_gauss<DIM, T>(__builtin_popcount(b ^ q));
-                uq += f * w[b];
-                lq += f * lam[b];
-            }
-            T e = exp(uq) * lq;
-#pragma unroll
-            for (int a = 0; a < NV; ++a) src[a] += e * phi_gauss<DIM, T>(__builtin_popcount(a ^ q));
-        }
+        for (int q = 0; q < NV; ++q) lq[q] *= exp(uq[q]);
+        gauss_interp<DIM, T>(lq, src);
         T lw = T(ph.a0) * wq;
 #pragma unroll
         for (int a = 0; a < NV; ++a) r[a] = hs * Kl[a] - lw * src[a];
