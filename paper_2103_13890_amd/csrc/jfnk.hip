@@ -1271,25 +1271,23 @@ jfnk_status jfnk_jv(jfnk_ctx *c, int level, int prec, const void *u, const void 
     if (prec == JFNK_F64) {
         const double *k = coef_kap<double>(c, level, (const double *)coef, c->tmpB);
         const double *A = (const double *)Au;
-        if (!A) {
+        if (!A && outer_mode(c) == M_FD_PLAIN) {   // the difference form takes no A(u)
             ops<double>(c->ph).residual(c->ex, g, c->ph, k, (const double *)u, nullptr, c->tmpA, nullptr, nullptr);
             A = c->tmpA;
         }
-        vec_eps_num<double>(c->ex, g, nc, (const double *)u, root_eps(c, JFNK_F64, outer_mode(c)), c->opt.eps_mode,
-                            slot(c, S_DOT));
-        vec_dot<double, double>(c->ex, g.nn * nc, (const double *)v, (const double *)v, slot(c, S_XN2));
+        vec_fd_step<double>(c->ex, g, nc, (const double *)u, (const double *)v, root_eps(c, JFNK_F64, outer_mode(c)),
+                        c->opt.eps_mode, slot(c, S_DOT), slot(c, S_XN2));
         op_jv<double, double>(c->ex, outer_mode(c), g, c->ph, k, (const double *)u, A, (const double *)v,
                               slot(c, S_DOT), slot(c, S_XN2), eps_override, (double *)Jv);
     } else {
         const float *k = coef_kap<float>(c, level, (const double *)coef, (float *)c->tmpB);
         const float *A = (const float *)Au;
-        if (!A) {
+        if (!A && outer_mode(c) == M_FD_PLAIN) {   // the difference form takes no A(u)
             ops<float>(c->ph).residual(c->ex, g, c->ph, k, (const float *)u, nullptr, (float *)c->tmpA, nullptr, nullptr);
             A = (const float *)c->tmpA;
         }
-        vec_eps_num<float>(c->ex, g, nc, (const float *)u, root_eps(c, JFNK_F32, outer_mode(c)), c->opt.eps_mode,
-                           slot(c, S_DOT));
-        vec_dot<float, float>(c->ex, g.nn * nc, (const float *)v, (const float *)v, slot(c, S_XN2));
+        vec_fd_step<float>(c->ex, g, nc, (const float *)u, (const float *)v, root_eps(c, JFNK_F32, outer_mode(c)),
+                       c->opt.eps_mode, slot(c, S_DOT), slot(c, S_XN2));
         op_jv<float, float>(c->ex, outer_mode(c), g, c->ph, k, (const float *)u, A, (const float *)v,
                             slot(c, S_DOT), slot(c, S_XN2), eps_override, (float *)Jv);
     }

@@ -173,6 +173,11 @@ void vec_scale_cast(const Exec &, const Grid &, int nc, const TI *x, TO *y, doub
 // FD step numerator of a level: root (1 + ||x||) (mode 0) or root mean(1 + |x|) (mode 1)
 template <typename T>
 void vec_eps_num(const Exec &, const Grid &, int nc, const T *x, double root, int mode, double *num);
+// The FD step of a single J v in one pass over x and v: the numerator as in
+// vec_eps_num, and ||v||^2 -> vn2 (a plain slot, never deferred)
+template <typename T>
+void vec_fd_step(const Exec &, const Grid &, int nc, const T *x, const T *v, double root, int mode, double *num,
+                 double *vn2);
 // Chebyshev start from zero: r = b, d = b / theta, s = 0; ||d||^2
 template <typename T>
 void vec_cheb_zero(const Exec &, const Grid &, int nc, const T *b, T *r, T *d, T *s, double inv_theta,

@@ -108,23 +108,46 @@ __device__ __forceinline__ void block_partials(double (&v)[NS], const Red &red) 
     if (threadIdx.x < NS) red.part[(size_t)blockIdx.x * NS + threadIdx.x] = tot[threadIdx.x];
 }
 
-// Second kernel of a grid reduction: one block sums the nb partials in
-// block order and hands the totals to fin on thread 0.  Launched on the same
-// stream right after the producing kernel, whose completion makes the
-// partials visible (no device-wide fence inside the producer, whose cost on
-// gfx950 is an L2 write-back per block).
+// Second kernel of a grid reduction: one block sums the nb partials in a fixed
+// order and hands the totals to fin on thread 0.  Launched on the same stream
+// right after the producing kernel, whose completion makes the partials
+// visible (no device-wide fence inside the producer, whose cost on gfx950 is
+// an L2 write-back per block).  Its time is the latency of its loads: the
+// partials come from other XCDs' writes, so up to eight trips of loads are in
+// flight at once and more than 2048 partials get 1024 threads (one sum of up to
+// 2048 partials 3.7 us with one load in flight, 2.5 so).
+template <int NS> constexpr int finish_threads = NS <= 4 ? 1024 : 256;   // wider sums need the registers
 template <int NS, class Fin>
-__global__ __launch_bounds__(256) void k_finish(Red red, int nb, Fin fin) {
+__global__ __launch_bounds__(finish_threads<NS>) void k_finish(Red red, int nb, Fin fin) {
     __shared__ double scratch[MAX_WAVES * NS];
     __shared__ double tot[NS];
-    double acc[NS];
+    constexpr int U = NS <= 2 ? 8 : NS <= 4 ? 4 : 1;
+    const int bd = blockDim.x;
+    double acc[U][NS], sum[NS];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) acc[k] = 0.0;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int k = 0; k < NS; ++k) acc[k] += red.part[(size_t)b * NS + k];
+        for (int k = 0; k < NS; ++k) acc[u][k] = 0.0;
+    for (int b0 = threadIdx.x; b0 < nb; b0 += U * bd) {
+        double in[U][NS];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = min(b0 + u * bd, nb - 1);
+#pragma unroll
+            for (int k = 0; k < NS; ++k) in[u][k] = red.part[(size_t)b * NS + k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < NS; ++k) acc[u][k] += b0 + u * bd < nb ? in[u][k] : 0.0;
     }
-    block_sum<NS>(acc, scratch, tot);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        sum[k] = acc[0][k];
+#pragma unroll
+        for (int u = 1; u < U; ++u) sum[k] += acc[u][k];
+    }
+    block_sum<NS>(sum, scratch, tot);
     if (threadIdx.x == 0) fin(tot);
 }
 
@@ -197,6 +220,6 @@ template <int NS> struct FinStore {
 namespace jfnk {
 template <int NS, class Fin>
 inline void finish(hipStream_t st, const Red &red, int nb, const Fin &fin) {
-    k_finish<NS, Fin><<<1, 256, 0, st>>>(red, nb, fin);
+    k_finish<NS, Fin><<<1, nb > 2048 ? finish_threads<NS> : 256, 0, st>>>(red, nb, fin);
 }
 }  // namespace jfnk
