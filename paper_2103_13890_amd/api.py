@@ -78,6 +78,7 @@ class Context:
         self.ncomp = 3 if problem.kind == _lib.NEOHOOKE else 1
         self.dim = problem.dim
         self.vprec = self.options.vcycle_prec
+        self._numel = {}     # (level, comps) -> entries of a level's array
 
     def _check(self, h, status):
         if status != _lib.OK:
@@ -91,6 +92,7 @@ class Context:
         if getattr(self, 'h', None):
             self.lib.jfnk_destroy(self.h)
             self.h = None
+            self._numel.clear()     # a closed context refuses every level again
 
     def __del__(self):
         try:
@@ -111,6 +113,17 @@ class Context:
         sh = (n[1] + 1, n[0] + 1) if self.dim == 2 else (n[2] + 1, n[1] + 1, n[0] + 1)
         return ((self.ncomp,) + sh) if (comps and self.ncomp > 1) else sh
 
+    def numel(self, level, comps=True):
+        """Entries of a level's array: fixed by the problem, so asked of the
+        library once per level (it took half the time of a small call)."""
+        want = self._numel.get((level, comps))
+        if want is None:
+            want = 1
+            for s in self.node_shape(level, comps):
+                want *= s
+            self._numel[level, comps] = want
+        return want
+
     def empty(self, level, dtype=torch.float64, comps=True):
         return torch.zeros(self.node_shape(level, comps), dtype=dtype, device=self.device)
 
@@ -129,9 +142,7 @@ def _ptr(t, ctx, level, dtype, comps=True, name='array'):
         raise TypeError(f'{name} has dtype {t.dtype}, expected {dtype}')
     if not t.is_contiguous():
         raise ValueError(f'{name} must be contiguous')
-    want = 1
-    for s in ctx.node_shape(level, comps):
-        want *= s
+    want = ctx.numel(level, comps)
     if t.numel() != want:
         raise ValueError(f'{name} has {t.numel()} entries, level {level} needs {want}')
     return ctypes.c_void_p(t.data_ptr())
