@@ -59,6 +59,14 @@ __device__ __forceinline__ void node_coords(const Grid &g, long long i, int &x, 
     z = (int)q2;
 }
 
+// Tile of block id of nb: ids are dealt round-robin over the 8 XCDs, and each
+// XCD owns a contiguous range of tiles.
+__device__ __forceinline__ int xcd_tile(int id, int nb) {
+    const int q = nb / 8, r = nb % 8;
+    const int xcd = id % 8, loc = id / 8;
+    return xcd < r ? xcd * (q + 1) + loc : r * (q + 1) + (xcd - r) * q + loc;
+}
+
 // Evaluation modes of the stencil kernels: the residual A(x), the FD
 // quotient from two residual evaluations, its element difference form, the
 // exact transposed Jacobian J(x)^T v, or the coefficient's (dA/dm)^T v without

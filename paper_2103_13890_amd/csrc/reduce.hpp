@@ -35,6 +35,17 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// value of lane l + 1 / l - 1 (0 beyond the wavefront)
+template <int CTRL, typename T> __device__ __forceinline__ T wave_shift(T v) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+    } else {
+        return dpp_mov<CTRL>(v);
+    }
+}
+template <typename T> __device__ __forceinline__ T from_right(T v) { return wave_shift<0x130>(v); }   // wave_shl:1
+template <typename T> __device__ __forceinline__ T from_left(T v) { return wave_shift<0x138>(v); }    // wave_shr:1
+
 // Sum over the 64 lanes of a wavefront (all lanes active), the same value in
 // every lane.  Inside a 16-lane row each step adds the value of a partner
 // lane whose partner is the lane itself (lane ^ 1, lane ^ 2, then the

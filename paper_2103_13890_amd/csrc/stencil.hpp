@@ -29,14 +29,6 @@
 
 namespace jfnk {
 
-// Tile of block id of nb: ids are dealt round-robin over the 8 XCDs, and each
-// XCD owns a contiguous range of tiles.
-__device__ __forceinline__ int xcd_tile(int id, int nb) {
-    const int q = nb / 8, r = nb % 8;
-    const int xcd = id % 8, loc = id / 8;
-    return xcd < r ? xcd * (q + 1) + loc : r * (q + 1) + (xcd - r) * q + loc;
-}
-
 // ---- epilogues ---------------------------------------------------------------
 // NS: number of grid sums; NCOMP: components; NIN: values read per node and
 // component; VIN: the index of the input that is the FD direction itself

@@ -18,17 +18,6 @@ namespace jfnk {
 
 constexpr int ROW2_COLS = 62;
 
-// value of lane l + 1 / l - 1 (0 beyond the wavefront)
-template <int CTRL, typename T> __device__ __forceinline__ T wave_shift(T v) {
-    if constexpr (sizeof(T) == 4) {
-        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-    } else {
-        return dpp_mov<CTRL>(v);
-    }
-}
-template <typename T> __device__ __forceinline__ T from_right(T v) { return wave_shift<0x130>(v); }   // wave_shl:1
-template <typename T> __device__ __forceinline__ T from_left(T v) { return wave_shift<0x138>(v); }    // wave_shr:1
-
 template <int KIND, int MODE, typename T, typename TV, class Epi, int PF, int R>
 __global__ __launch_bounds__(BLOCK) void k_row2(Grid g, Phys ph, const T *kap, const T *x, const TV *v, const T *Ax,
                                                 FdStep fd, Epi epi, Red red, int strips, int tiles) {

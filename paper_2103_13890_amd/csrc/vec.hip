@@ -714,78 +714,57 @@ template void tr_project<double, double>(const Exec &, const Grid &, const Grid 
 template void tr_project<double, float>(const Exec &, const Grid &, const Grid &, int, const double *, float *);
 template void tr_project<float, float>(const Exec &, const Grid &, const Grid &, int, const float *, float *);
 
-// R = I^T with zero rows at coarse Dirichlet nodes
-template <typename T>
-__global__ void k_restrict(Grid gf, Grid gc, int nc, const T *rf, T *rc, Red red, double *out) {
+// Two neighbours of a grid row.  Rows have odd lengths, so a pair is aligned
+// to one entry only, which the vector loads and stores accept.
+template <typename T> struct alignas(sizeof(T)) XPair { T a, b; };
+
+// R = I^T with zero rows at coarse Dirichlet nodes: the 3^DIM fine neighbours
+// of a coarse node with weights (1/2, 1, 1/2) per axis, as straight-line code.
+// A fine row gives a pair per lane, whose left neighbour comes from the lane to
+// the left (lane 0 loads it); rows off the grid are clamped and count 0.  Bound
+// by the loads' passage through L1: with three loads per row 256^3 took 32 us in
+// FP32 and 40 in FP64, with pairs and a load of the neighbour 36 and 41, so 24
+// and 33; all nine rows in flight need registers that halve the waves (34 and
+// 48).  Blocks in XCD-contiguous order share fine rows in their L2.
+template <int DIM, typename T>
+__global__ __launch_bounds__(BLOCK) void k_restrict(Grid gf, Grid gc, int nc, const T *rf, T *rc, Red red,
+                                                    double *out) {
     double sm[1] = {0.0};
-    GRID_STRIDE(i, gc.nn) {
-        int cx, cy, cz;
-        node_coords(gc, i, cx, cy, cz);
-        const bool dd = is_dirichlet(gc, cx, cy, cz);
-        const int zlo = gc.dim == 3 ? -1 : 0, zhi = gc.dim == 3 ? 1 : 0;
+    const long long step = (long long)gridDim.x * BLOCK;
+    for (long long i = (long long)xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x; i < gc.nn; i += step) {
+        int X, Y, Z;
+        node_coords(gc, i, X, Y, Z);
+        const bool dd = is_dirichlet(gc, X, Y, Z), last = X == gc.NX - 1;
+        const int x = 2 * X - (last ? 1 : 0), xl = max(2 * X - 1, 0);
+        const bool first = (threadIdx.x & 63) == 0;
         for (int c = 0; c < nc; ++c) {
+            const T *r = rf + c * gf.nn;
             T acc = T(0);
-            if (!dd) {
-                for (int dz = zlo; dz <= zhi; ++dz) {
-                    const int fz = 2 * cz + dz;
-                    if (fz < 0 || fz >= gf.NZ) continue;
-                    const T wz = dz == 0 ? T(1) : T(0.5);
-                    for (int dy = -1; dy <= 1; ++dy) {
-                        const int fy = 2 * cy + dy;
-                        if (fy < 0 || fy >= gf.NY) continue;
-                        const T wy = wz * (dy == 0 ? T(1) : T(0.5));
-                        for (int dx = -1; dx <= 1; ++dx) {
-                            const int fx = 2 * cx + dx;
-                            if (fx < 0 || fx >= gf.NX) continue;
-                            acc += wy * (dx == 0 ? T(1) : T(0.5)) * rf[c * gf.nn + node_index(gf, fx, fy, fz)];
-                        }
-                    }
+#pragma unroll 1
+            for (int a = 0; a < (DIM == 3 ? 3 : 1); ++a) {
+                const int z = DIM == 3 ? 2 * Z + a - 1 : 0, zc = min(max(z, 0), gf.NZ - 1);
+                XPair<T> pr[3];
+                T left[3] = {T(0), T(0), T(0)}, pz = T(0);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const int yc = min(max(2 * Y + b - 1, 0), gf.NY - 1);
+                    const T *row = r + ((long long)zc * gf.NY + yc) * gf.NX;
+                    pr[b] = *(const XPair<T> *)(row + x);
+                    if (first) left[b] = row[xl];
                 }
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const int y = 2 * Y + b - 1;
+                    const T sh = from_left(pr[b].b), l = X > 0 ? (first ? left[b] : sh) : T(0), m = last ? pr[b].b : pr[b].a, rt = last ? T(0) : pr[b].b;
+                    const T px = T(0.5) * l + m + T(0.5) * rt;
+                    pz += (b == 1 ? T(1) : T(0.5)) * (y >= 0 && y < gf.NY ? px : T(0));
+                }
+                acc += (DIM == 2 || a == 1 ? T(1) : T(0.5)) * (DIM == 2 || z == zc ? pz : T(0));
             }
+            if (dd) acc = T(0);
             rc[c * gc.nn + i] = acc;
             sm[0] += (double)acc * (double)acc;
         }
-    }
-    if (out) block_partials<1>(sm, red);
-}
-// 3D, one component: the 27 fine neighbours of a coarse node with weights
-// (1/2, 1, 1/2) per axis, as straight-line code; indices are clamped into the
-// grid and the weight of a clamped neighbour is 0.
-template <typename T>
-__global__ __launch_bounds__(BLOCK) void k_restrict3(Grid gf, Grid gc, const T *rf, T *rc, Red red, double *out) {
-    double sm[1] = {0.0};
-    GRID_STRIDE(i, gc.nn) {
-        int cx, cy, cz;
-        node_coords(gc, i, cx, cy, cz);
-        T acc = T(0);
-        if (!is_dirichlet(gc, cx, cy, cz)) {
-            int ix[3], iy[3], iz[3];
-            T wx[3], wy[3], wz[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int fx = 2 * cx + d - 1, fy = 2 * cy + d - 1, fz = 2 * cz + d - 1;
-                const T w = d == 1 ? T(1) : T(0.5);
-                wx[d] = (fx >= 0 && fx < gf.NX) ? w : T(0);
-                wy[d] = (fy >= 0 && fy < gf.NY) ? w : T(0);
-                wz[d] = (fz >= 0 && fz < gf.NZ) ? w : T(0);
-                ix[d] = min(max(fx, 0), gf.NX - 1);
-                iy[d] = min(max(fy, 0), gf.NY - 1);
-                iz[d] = min(max(fz, 0), gf.NZ - 1);
-            }
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                T pz = T(0);
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const T *row = rf + ((long long)iz[a] * gf.NY + iy[b]) * gf.NX;
-                    const T px = wx[0] * row[ix[0]] + wx[1] * row[ix[1]] + wx[2] * row[ix[2]];
-                    pz += wy[b] * px;
-                }
-                acc += wz[a] * pz;
-            }
-        }
-        rc[i] = acc;
-        sm[0] += (double)acc * (double)acc;
     }
     if (out) block_partials<1>(sm, red);
 }
@@ -794,88 +773,81 @@ template <typename T>
 void tr_restrict(const Exec &ex, const Grid &gf, const Grid &gc, int nc, const T *rf, T *rc, double *nrm2) {
     const int nb = vblocks(gc.nn);
     const Red r = red_for(ex, nrm2, nb);
-    if (gf.dim == 3 && nc == 1) k_restrict3<T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, rf, rc, r, nrm2);
-    else k_restrict<T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, rf, rc, r, nrm2);
+    if (gf.dim == 3) k_restrict<3, T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, rf, rc, r, nrm2);
+    else k_restrict<2, T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, rf, rc, r, nrm2);
     if (nrm2) finish_to<1>(ex, nrm2, r, nb, FinStore<1>{nrm2});
 }
 template void tr_restrict<float>(const Exec &, const Grid &, const Grid &, int, const float *, float *, double *);
 template void tr_restrict<double>(const Exec &, const Grid &, const Grid &, int, const double *, double *, double *);
 
-// s_f += I c: even fine index -> coarse f/2 (weight 1), odd -> both neighbours (1/2)
-template <typename T>
-__global__ void k_prolong_add(Grid gf, Grid gc, int nc, const T *cc, T *sf, Red red, double *out) {
+// s_f += I c: even fine index -> coarse f/2 (weight 1), odd -> both neighbours
+// (1/2).  A thread owns the 2^DIM fine nodes 2X .. 2X + 1 (and y, z) of a coarse
+// node: they share the index arithmetic and the 2^DIM coarse values, and their
+// rows are read and written by pairs: at 256^3 28 us in FP32 and 47 in FP64
+// (5 and 6 TB/s, part of it from the last-level cache), where one thread per
+// fine node, bound by its index arithmetic, took 59 and 91.
+template <int DIM, typename T>
+__global__ __launch_bounds__(BLOCK) void k_prolong_add(Grid gf, Grid gc, int nc, const T *cc, T *sf, Red red,
+                                                       double *out) {
+    constexpr int NV = 1 << DIM;
     double sm[1] = {0.0};
-    GRID_STRIDE(i, gf.nn) {
-        int fx, fy, fz;
-        node_coords(gf, i, fx, fy, fz);
-        const bool dd = is_dirichlet(gf, fx, fy, fz);
-        const int x0 = fx >> 1, x1 = (fx + 1) >> 1, y0 = fy >> 1, y1 = (fy + 1) >> 1;
-        const int z0 = fz >> 1, z1 = (fz + 1) >> 1;
-        const T wx = (fx & 1) ? T(0.5) : T(1), wy = (fy & 1) ? T(0.5) : T(1), wz = (fz & 1) ? T(0.5) : T(1);
+    const long long step = (long long)gridDim.x * BLOCK;
+    for (long long i = (long long)xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x; i < gc.nn; i += step) {
+        int X, Y, Z;
+        node_coords(gc, i, X, Y, Z);
+        const bool last = X == gc.NX - 1;
+        const int X1 = min(X + 1, gc.NX - 1);
         for (int c = 0; c < nc; ++c) {
-            const long long k = c * gf.nn + i;
-            if (dd) {
-                sf[k] = T(0);
-                continue;
-            }
             const T *cb = cc + c * gc.nn;
-            T v = T(0);
-            // (x0,x1) coincide for even fx: count the node once with weight 1
-            const int nxs = (fx & 1) ? 2 : 1, nys = (fy & 1) ? 2 : 1, nzs = (gf.dim == 3 && (fz & 1)) ? 2 : 1;
-            for (int a = 0; a < nzs; ++a)
-                for (int b = 0; b < nys; ++b)
-                    for (int d = 0; d < nxs; ++d) {
-                        const int X = d ? x1 : x0, Y = b ? y1 : y0, Z = a ? z1 : z0;
-                        v += wx * wy * wz * cb[node_index(gc, X, Y, Z)];
-                    }
-            T s = sf[k] + v;
-            sf[k] = s;
-            sm[0] += (double)s * (double)s;
-        }
-    }
-    if (out) block_partials<1>(sm, red);
-}
-// 3D, one component: the (up to) 8 coarse corners of the fine node's
-// coarse cell as straight-line code.  On an even fine coordinate both coarse
-// indices coincide and the weights are (1, 0); on an odd one (1/2, 1/2).
-template <typename T>
-__global__ __launch_bounds__(BLOCK) void k_prolong_add3(Grid gf, Grid gc, const T *cc, T *sf, Red red,
-                                                        double *out) {
-    double sm[1] = {0.0};
-    GRID_STRIDE(i, gf.nn) {
-        int fx, fy, fz;
-        node_coords(gf, i, fx, fy, fz);
-        T sv = T(0);
-        if (!is_dirichlet(gf, fx, fy, fz)) {
-            const int X[2] = {fx >> 1, (fx + 1) >> 1}, Y[2] = {fy >> 1, (fy + 1) >> 1}, Z[2] = {fz >> 1, (fz + 1) >> 1};
-            const T wx[2] = {(fx & 1) ? T(0.5) : T(1), (fx & 1) ? T(0.5) : T(0)};
-            const T wy[2] = {(fy & 1) ? T(0.5) : T(1), (fy & 1) ? T(0.5) : T(0)};
-            const T wz[2] = {(fz & 1) ? T(0.5) : T(1), (fz & 1) ? T(0.5) : T(0)};
-            T v = T(0);
+            T *sb = sf + c * gf.nn;
+            T q[NV];
+            XPair<T> pr[NV / 2];
+            T *row[NV / 2];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                T py = T(0);
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const T *row = cc + ((long long)Z[a] * gc.NY + Y[b]) * gc.NX;
-                    py += wy[b] * (wx[0] * row[X[0]] + wx[1] * row[X[1]]);
-                }
-                v += wz[a] * py;
+            for (int k = 0; k < NV / 2; ++k) {
+                const int dy = k & 1, dz = k >> 1;
+                const T *cr = cb + ((long long)min(Z + dz, gc.NZ - 1) * gc.NY + min(Y + dy, gc.NY - 1)) * gc.NX;
+                q[2 * k] = cr[X];
+                q[2 * k + 1] = cr[X1];
+                row[k] = sb + ((long long)min(2 * Z + dz, gf.NZ - 1) * gf.NY + min(2 * Y + dy, gf.NY - 1)) * gf.NX + 2 * X;
             }
-            sv = sf[i] + v;
+            if (last) {
+#pragma unroll
+                for (int k = 0; k < NV / 2; ++k) pr[k] = XPair<T>{row[k][0], T(0)};
+            } else {
+#pragma unroll
+                for (int k = 0; k < NV / 2; ++k) pr[k] = *(const XPair<T> *)row[k];
+            }
+#pragma unroll
+            for (int k = 0; k < DIM; ++k)
+#pragma unroll
+                for (int a = 0; a < NV; ++a)
+                    if ((a >> k) & 1) q[a] = T(0.5) * q[a ^ (1 << k)] + T(0.5) * q[a];
+#pragma unroll
+            for (int k = 0; k < NV / 2; ++k) {
+                const int y = 2 * Y + (k & 1), z = 2 * Z + (k >> 1);
+                if (y >= gf.NY || z >= gf.NZ) continue;
+                const T s0 = is_dirichlet(gf, 2 * X, y, z) ? T(0) : pr[k].a + q[2 * k];
+                const T s1 = is_dirichlet(gf, 2 * X + 1, y, z) ? T(0) : pr[k].b + q[2 * k + 1];
+                sm[0] += (double)s0 * (double)s0;
+                if (last) {
+                    row[k][0] = s0;
+                } else {
+                    *(XPair<T> *)row[k] = XPair<T>{s0, s1};
+                    sm[0] += (double)s1 * (double)s1;
+                }
+            }
         }
-        sf[i] = sv;
-        sm[0] += (double)sv * (double)sv;
     }
     if (out) block_partials<1>(sm, red);
 }
 
 template <typename T>
 void tr_prolong_add(const Exec &ex, const Grid &gf, const Grid &gc, int nc, const T *cc, T *sf, double *nrm2) {
-    const int nb = vblocks(gf.nn);
+    const int nb = vblocks(gc.nn);
     const Red r = red_for(ex, nrm2, nb);
-    if (gf.dim == 3 && nc == 1) k_prolong_add3<T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, cc, sf, r, nrm2);
-    else k_prolong_add<T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, cc, sf, r, nrm2);
+    if (gf.dim == 3) k_prolong_add<3, T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, cc, sf, r, nrm2);
+    else k_prolong_add<2, T><<<nb, BLOCK, 0, ex.st>>>(gf, gc, nc, cc, sf, r, nrm2);
     if (nrm2) finish_to<1>(ex, nrm2, r, nb, FinStore<1>{nrm2});
 }
 template void tr_prolong_add<float>(const Exec &, const Grid &, const Grid &, int, const float *, float *, double *);
