@@ -9,8 +9,8 @@
 // square roots and two quotients per p = 1 element, eight exponentials per
 // Bratu element); the halo costs (R + 1)/R in y and 64/62 in x.  All rows of
 // the tile are loaded before the first element.  One FP64 Chebyshev step at
-// 800^2: Bratu 37.2 -> 19.1 us, minimal surface 31.8 -> 13.5 us; at 1600^2 125
-// -> 53 and 88 -> 37 us.
+// 800^2: Bratu 37.2 -> 19.1 us (14.3 since its expm1 is a series), minimal
+// surface 31.8 -> 12.3 us; at 1600^2 125 -> 53 (40) and 88 -> 36 us.
 #pragma once
 #include "stencil.hpp"
 
