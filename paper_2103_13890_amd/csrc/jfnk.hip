@@ -381,9 +381,8 @@ template <typename T> jfnk_status power_method(jfnk_ctx *c, int l) {
         const double *n2 = k == 1 ? lslot(c, l, L_V) : lslot(c, l, pq[(k - 1) % 3] + 1);
         double *out = lslot(c, l, pq[k % 3]);
         ops<T>(c->ph).power(c->ex, mg_mode(c), g, c->ph, CP<T>(L.kap), CP<T>(L.x), CP<T>(L.Ax), buf[(k - 1) % 4],
-                    lslot(c, l, L_NUM), n2, buf[k % 4], out);
+                    lslot(c, l, L_NUM), n2, buf[k % 4], out, c->hpin + 2 * (k % 3));
         CHK(check_launch(c));
-        HIPCHK(c, hipMemcpyAsync(c->hpin + 2 * (k % 3), out, 2 * sizeof(double), hipMemcpyDeviceToHost, c->st));
         HIPCHK(c, hipEventRecord(c->pev[k % 3], c->st));
         queued = k;
         return JFNK_OK;

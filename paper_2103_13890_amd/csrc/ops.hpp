@@ -107,7 +107,8 @@ size_t nh_scratch_entries(const Grid &);
 //   ||sout||^2 -> s_nrm2 (nullable).  sout may alias s.
 // cheb_init: start from s: r = b - J s, d = r / theta
 // resid_jv, a7: residual of the correction, t = b - J s
-// power, a4: power step: q = J v, out[0] = v.q, out[1] = ||q||^2
+// power, a4: power step: q = J v, out[0] = v.q, out[1] = ||q||^2, both also to
+// host[0..1] (page-locked host memory, readable once the stream has passed it)
 template <typename T> struct StencilTable {
     void (*residual)(const Exec &, const Grid &, const Phys &, const T *kap, const T *u, const T *b, T *F, T *Aout,
                      double *nrm2);
@@ -128,7 +129,7 @@ template <typename T> struct StencilTable {
     void (*resid_jv)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
                      const T *s, const double *num, const double *vn2, const T *b, T *t);
     void (*power)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
-                  const T *v, const double *num, const double *vn2, T *q, double *out);
+                  const T *v, const double *num, const double *vn2, T *q, double *out, double *host);
     void (*jv_mixed)(const Exec &, int mode, const Grid &, const Phys &, const T *kap, const T *x, const T *Ax,
                      const float *v, const double *num, const double *vn2, double eps_fixed, T *Jv);
     // FP64: a13, exact J(u)^T lam on the DoFs; a14, scale (dF/dm)^T lam at every

@@ -287,6 +287,7 @@ template <typename T, int NC> struct EpiPower {
     T *q;
     long long nn;
     double *out;
+    double *host;        // the same two values, in page-locked host memory
     double sc = 0.0;     // 1/||v||, set on the device from the step's norm
     __device__ __forceinline__ void prepare(double n2) { sc = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0; }
     template <bool SKIPV = false, class At> __device__ __forceinline__ void load(const At &at, T *in) const {
@@ -304,7 +305,10 @@ template <typename T, int NC> struct EpiPower {
             sm[1] += (double)qk * (double)qk;
         }
     }
-    __device__ void operator()(const double *t) const { out[0] = t[0]; out[1] = t[1]; }
+    __device__ void operator()(const double *t) const {
+        out[0] = host[0] = t[0];
+        out[1] = host[1] = t[1];
+    }
     double *slot() const { return out; }
 };
 
