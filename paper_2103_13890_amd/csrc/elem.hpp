@@ -242,8 +242,7 @@ __device__ __forceinline__ void elem_plap_gauss(const T *w, const Phys &ph, T h,
 #pragma unroll
         for (int j = 0; j < NH; ++j) F[i][j] = G[i][j] * gq_pair<DIM, T>(k, i, j);
     const T hs = (DIM == 3) ? h : T(1);
-    const bool on = m != T(0);
-    gq_scatter<DIM, T>(F, on ? m * hs * T(1.0 / NV) : T(0), r);
+    gq_scatter<DIM, T>(F, m * hs * T(1.0 / NV), r);
 }
 
 // PLAP_GAUSS FD quotient in difference form: per Gauss point, with the mean
@@ -278,8 +277,7 @@ __device__ __forceinline__ void elem_plap_gauss_fd(const T *x, const T *v, T eps
         for (int j = 0; j < NH; ++j)
             F[i][j] = Gv[i][j] * gq_pair<DIM, T>(k, i, j) + G[i][j] * gq_pair<DIM, T>(dk, i, j);
     const T hs = (DIM == 3) ? h : T(1);
-    const bool on = m != T(0);
-    gq_scatter<DIM, T>(F, on ? m * hs * T(1.0 / NV) : T(0), q_out);
+    gq_scatter<DIM, T>(F, m * hs * T(1.0 / NV), q_out);
 }
 
 // PLAP_GAUSS exact J_e lam (symmetric): per Gauss point
@@ -311,10 +309,9 @@ __device__ __forceinline__ void elem_plap_gauss_vjp(const T *w, const T *lam, co
 // ---------------------------------------------------------------------------
 // scalar kinds: r[a] for one element.  w: state corners, kap: e^{m} corners
 // ---------------------------------------------------------------------------
-// m multiplies the whole element vector (0 switches an element off without
-// a branch).  A switched-off element may have a degenerate state (no
-// gradient at delta = 0), so its nonlinear coefficient is selected away
-// rather than multiplied by 0.
+// m multiplies the whole element vector: 0 switches an element off without a
+// branch.  The caller gives such an element corners at which it is finite
+// wherever the elements of the same nodes are.
 template <int DIM, int KIND, typename T, int PF = 0>
 __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys &ph, T h, T *r, T m = T(1)) {
     if constexpr (KIND == JFNK_PLAP_GAUSS) {
@@ -326,7 +323,7 @@ __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys
     T Ku[NV];
     stiff_apply_s<DIM, T>(w, Ku);                 // KS K u
     const T hs = (DIM == 3) ? h : T(1);          // h^(d-2)
-    const T hk = hs * T(1.0 / KS) * m;
+    const T hk = hs * T(1.0 / KS) * m;            // undoes KS
     if (KIND == JFNK_BRATU) {
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
@@ -346,7 +343,6 @@ __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys
         T s = quad * (T(1) / (T(KS) * h * h));
         T d2 = T(ph.a1) * T(ph.a1);
         T k = plap_pow<T, PF>(d2 + s, ph.a0, 0) * hk;
-        if (!(m != T(0))) k = T(0);
 #pragma unroll
         for (int a = 0; a < NV; ++a) r[a] = k * Ku[a];
     } else {  // INVCOEF
@@ -355,7 +351,6 @@ __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys
         for (int a = 0; a < NV; ++a) { ks += kap[a]; us += w[a]; }
         T kb = ks / T(NV), ub = us / T(NV);
         T k = kb * (T(1) + ub * ub) * hk;
-        if (!(m != T(0))) k = T(0);
 #pragma unroll
         for (int a = 0; a < NV; ++a) r[a] = k * Ku[a];
     }
@@ -458,8 +453,7 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
         kw = kb * (T(1) + wb * wb);
         dk = kb * vb * (T(2) * xb + eps * vb);
     }
-    const bool on = m != T(0);
-    const T cv = on ? hk * kw : T(0), cx = on ? hk * dk : T(0);
+    const T cv = hk * kw, cx = hk * dk;
 #pragma unroll
     for (int a = 0; a < NV; ++a) q[a] = cv * Kv[a] + cx * Kx[a];
 }

@@ -328,8 +328,8 @@ template <class E> __device__ __forceinline__ double fd_eps_prepare(const FdStep
 }
 
 // ---- one element in any mode ------------------------------------------------------
-// xe: state corners; ve: direction corners (FD modes); r: output contributions
-// m (scalar kinds): multiplies the element vector; 0 switches the element off
+// xe: state corners; ve: direction corners (FD modes); r: output contributions;
+// m (scalar kinds): multiplies the element vector, 0 switches the element off
 template <int DIM, int KIND, int MODE, typename T, int NC, int NV, int PF = 0>
 __device__ __forceinline__ void elem_eval(const T (*xe)[NV], const T (*ve)[NV], const T *kp, T eps,
                                           const Phys &ph, T h, T (*r)[NV], T m = T(1)) {

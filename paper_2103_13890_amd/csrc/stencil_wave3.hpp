@@ -6,8 +6,12 @@
 // a wave owns column 62 s + l - 1 of that numbering, so no lane idles at the
 // end of a grid row.  A lane evaluates the element column to its right: the
 // corner values of the next column and the contributions to it cross by
-// wavefront shifts (DPP); where the next lane starts another group the
-// element is off the grid and switched off.  The y neighbours of a node are
+// wavefront shifts (DPP).  Infinities and NaN stay with the nodes of their own
+// elements: where the next lane starts another group the element has corners
+// far apart, and what it gives to either side is selected away at the node; in
+// the rows off the grid the element is the mirror image of the one at the edge
+// (its rows are loaded mirrored), so that the factor 0 that switches it off meets
+// an infinity or a NaN only where that element has one.  The y neighbours of a node are
 // summed in registers along the lane's R + 1 elements of a layer, the z
 // neighbours by a register carry from layer to layer, so every element of a
 // tile is evaluated once.  The planes z and z + 1 of the state (and direction
@@ -69,18 +73,19 @@ __global__ __launch_bounds__(BLOCK) void k_wave3(Grid g, Phys ph, const T *kap, 
         const bool in_ = p >= 0 && Y0 < g.NY;
         const bool xdir = ((g.dir & JFNK_FACE_XLO) && X == 0) || ((g.dir & JFNK_FACE_XHI) && X == g.nx);
         const int nxy = g.NX * g.NY;
+        const bool xin = in_ && X < g.nx;       // the element column right of X exists
         // per-lane masks: fr[r] the direction is free in row Y0 - 1 + r, el[r] the
-        // element right of that row exists, own[k] the lane stores row Y0 + k,
+        // element row above that row exists, own[k] the lane stores row Y0 + k,
         // dr[k] that row's node is on a Dirichlet face in x or y
         unsigned col[R + 2];
         bool fr[R + 2], el[R + 1], own[R], dr[R];
 #pragma unroll
         for (int r = 0; r < R + 2; ++r) {
-            const int Y = Y0 - 1 + r, Yc = min(max(Y, 0), g.ny);
-            col[r] = (unsigned)(Yc * g.NX + X);
-            const bool yd = ((g.dir & JFNK_FACE_YLO) && Y == 0) || ((g.dir & JFNK_FACE_YHI) && Y == g.ny);
-            fr[r] = in_ && Y == Yc && !yd && !xdir;
-            if (r <= R) el[r] = in_ && X < g.nx && Y >= 0 && Y < g.ny;
+            const int Y = Y0 - 1 + r, Ym = Y < 0 ? 1 : Y > g.ny ? max(2 * g.ny - Y, 0) : Y;
+            col[r] = (unsigned)(Ym * g.NX + X);
+            const bool yd = ((g.dir & JFNK_FACE_YLO) && Ym == 0) || ((g.dir & JFNK_FACE_YHI) && Ym == g.ny);
+            fr[r] = in_ && !yd && !xdir;
+            if (r <= R) el[r] = Y >= 0 && Y < g.ny;
             if (r >= 1 && r <= R) {
                 own[r - 1] = in_ && lane >= 1 && lane <= ROW2_COLS && Y <= g.ny;
                 dr[r - 1] = xdir || yd;
@@ -181,7 +186,7 @@ __global__ __launch_bounds__(BLOCK) void k_wave3(Grid g, Phys ph, const T *kap, 
             const bool zd = zdir(z);
 #pragma unroll
             for (int k = 0; k < R; ++k) {
-                T val[1] = {O[k] + from_left(T1[k])};
+                T val[1] = {(xin ? O[k] : T(0)) + from_left(xin ? T1[k] : T(0))};
                 const bool dir = MODE != M_COEF && (zd || dr[k]);
                 if constexpr (PLAIN) val[0] = (val[0] - pax[k]) * ie;
                 if (dir || zero_fd) val[0] = T(0);
