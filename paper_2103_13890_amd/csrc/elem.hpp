@@ -109,7 +109,13 @@ template <typename T> __device__ __forceinline__ T hw_div(T a, T b) { return a /
 template <> __device__ __forceinline__ float hw_div<float>(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
 // (delta^2 + s)^e for the exponents the p-Laplacian needs
-// PF = 3, 1: the exponent p is known at compile time; PF = 0: read p.
+// PF: what is known of the exponent p at compile time: 3, 2 or 1 its value,
+// PF_GENERAL none of these, 0 nothing.  A branch on p inside an element's
+// unrolled points takes the registers of its widest side beside those of all
+// the others: the FP64 Gauss-point Chebyshev step of the black-box quotient has
+// 256 + 32 registers with all four sides at two rows per wave, 197 with the
+// general one alone.
+constexpr int PF_GENERAL = -1;
 template <typename T, int PF = 0>
 __device__ __forceinline__ T plap_pow(T base, double p, int which) {
     // which 0: (p-2)/2, 1: p/2, 2: (p-4)/2
@@ -117,8 +123,8 @@ __device__ __forceinline__ T plap_pow(T base, double p, int which) {
         T r = hw_sqrt(base);
         return which == 0 ? r : (which == 1 ? base * r : hw_div(T(1), r));
     }
-    if (PF == 0 && p == 2.0) return which == 0 ? T(1) : (which == 1 ? base : hw_div(T(1), base));
-    if (PF == 1 || p == 1.0) {     // the minimal-surface energy: exponents -1/2, 1/2, -3/2
+    if (PF == 2 || (PF == 0 && p == 2.0)) return which == 0 ? T(1) : (which == 1 ? base : hw_div(T(1), base));
+    if (PF == 1 || (PF == 0 && p == 1.0)) {     // the minimal-surface energy: exponents -1/2, 1/2, -3/2
         T r = hw_sqrt(base);
         return which == 1 ? r : hw_div(T(1), which == 0 ? r : base * r);
     }
@@ -204,10 +210,10 @@ __device__ __forceinline__ void plap_pair(T bx, T dsq, T eps, double p, T &kw, T
         const T kx = hw_sqrt(bx);
         kw = hw_sqrt(bw);
         dk = hw_div(dsq, kw + kx);
-    } else if (PF == 0 && p == 2.0) {
+    } else if (PF == 2 || (PF == 0 && p == 2.0)) {
         kw = T(1);
         dk = T(0);
-    } else if (PF == 1 || p == 1.0) {   // the minimal surface, k = b^(-1/2):
+    } else if (PF == 1 || (PF == 0 && p == 1.0)) {   // the minimal surface, k = b^(-1/2):
         // (k_w - k_x) / eps = -dsq / (s_x s_w (s_x + s_w)), s = sqrt(b)
         const T sx = hw_sqrt(bx), sw = hw_sqrt(bw);
         kw = hw_div(T(1), sw);
