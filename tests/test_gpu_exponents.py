@@ -50,3 +50,37 @@ def test_coarse_solves(params, n, prec):
     Js = api.jfnk_jv(ctx, 0, api.mg_get_level(ctx, 0, 'x'), s)
     r = (b - Js).double()
     assert float(r.norm()) <= bar * float(b.double().norm())
+
+
+@pytest.mark.parametrize('kind', ['plap', 'plap_gauss'])
+@pytest.mark.parametrize('params', EXPONENTS)
+@pytest.mark.parametrize('n', [(30, 12, 6), (62, 10, 8), (96, 92, 64)])
+def test_wave_kernels(kind, params, n):
+    """The 3D wave kernel's instances against the node-centric kernel, which reads
+    the exponent: F, J v in both forms and the VJP to 1e-12 in FP64 (the same
+    element values summed in another order; the black-box quotient divides a
+    difference of two such sums by a step of 1e-4, so 1e-8), a smoother of degree 4 to
+    1e-10, FP32 to 1e-4 (J v by the difference form)."""
+    nlevels = 3 if n[0] == 96 else 2      # the coarsest grid has at most 65,536 nodes
+    top = nlevels - 1
+    w, u, v = _workload(kind, params, n, [(0, 0), (1, 0), (2, 1)], nlevels)
+    U, V = to_dev(u), to_dev(v)
+
+    def rel(call):
+        a, b = call(2), call(1)
+        return float((a - b).norm() / b.norm())
+
+    def jv(path, form, x, d):
+        return api.jfnk_jv(make_ctx(w, kernel_path=path, fd_form=form), top, x, d, None, None, 1e-4)
+
+    def smooth(path):
+        c = make_ctx(w, kernel_path=path)
+        api.mg_setup(c, U)
+        return api.mg_smooth(c, top, V, torch.zeros_like(V), 4, True)
+    assert rel(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U)) < 1e-12
+    assert rel(lambda p: api.jfnk_vjp(make_ctx(w, kernel_path=p), top, 0, U, V)) < 1e-12
+    assert rel(lambda p: jv(p, 2, U, V)) < 1e-12
+    assert rel(lambda p: jv(p, 1, U, V)) < 1e-8
+    assert rel(smooth) < 1e-10
+    assert rel(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U.float())) < 1e-4
+    assert rel(lambda p: jv(p, 2, U.float(), V.float())) < 1e-4
