@@ -63,7 +63,12 @@ __device__ __forceinline__ void stiff_apply_s(const T *u, T *Ku) {
 // Values of a Q1 field at the tensor Gauss points from its corner values, axis
 // by axis (three operations per pair).  The operator is symmetric: it also
 // sums Gauss-point values against the basis functions at the corners.
-template <int DIM, typename T> __device__ __forceinline__ void gauss_interp(const T *u, T *uq) {
+// WEIGHTS: the pair by its two weights (four operations), so that a corner of
+// minus infinity makes the points around minus infinity and not NaN: for the
+// arguments of exp and expm1, which are finite there.  A degree-4 FP64 Bratu
+// smoother at 800^2 takes 58.9 us for 58.3; by the ratio of the weights and
+// one scale per point, with no more operations than by the difference, 59.1.
+template <int DIM, typename T, bool WEIGHTS = false> __device__ __forceinline__ void gauss_interp(const T *u, T *uq) {
 #pragma unroll
     for (int a = 0; a < (1 << DIM); ++a) uq[a] = u[a];
 #pragma unroll
@@ -72,9 +77,15 @@ template <int DIM, typename T> __device__ __forceinline__ void gauss_interp(cons
         for (int a = 0; a < (1 << DIM); ++a)
             if (!((a >> k) & 1)) {
                 const int b = a | (1 << k);
-                const T t = T(GL0) * (uq[b] - uq[a]);
-                uq[a] += t;
-                uq[b] -= t;
+                if (WEIGHTS) {
+                    const T lo = uq[a], hi = uq[b];
+                    uq[a] = T(GL1) * lo + T(GL0) * hi;
+                    uq[b] = T(GL0) * lo + T(GL1) * hi;
+                } else {
+                    const T t = T(GL0) * (uq[b] - uq[a]);
+                    uq[a] += t;
+                    uq[b] -= t;
+                }
             }
 }
 
@@ -334,7 +345,7 @@ __device__ __forceinline__ void elem_scalar(const T *w, const T *kap, const Phys
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
         T uq[NV], src[NV];
-        gauss_interp<DIM, T>(w, uq);
+        gauss_interp<DIM, T, true>(w, uq);
 #pragma unroll
         for (int q = 0; q < NV; ++q) uq[q] = exp(uq[q]);
         gauss_interp<DIM, T>(uq, src);
@@ -385,7 +396,7 @@ __device__ __forceinline__ T elem_scalar_energy(const T *w, const Phys &ph, T h)
     T vol = (DIM == 3) ? h * h * h : h * h;
     if (KIND == JFNK_BRATU) {
         T uq[NV], acc = T(0);
-        gauss_interp<DIM, T>(w, uq);
+        gauss_interp<DIM, T, true>(w, uq);
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc += exp(uq[q]);
         return T(0.5) * hs * quad - T(ph.a0) * (vol / T(NV)) * acc;
@@ -424,8 +435,8 @@ __device__ __forceinline__ void elem_scalar_fd(const T *x, const T *v, const T *
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
         T xq[NV], vq[NV], dq[NV], src[NV];
-        gauss_interp<DIM, T>(x, xq);
-        gauss_interp<DIM, T>(v, vq);
+        gauss_interp<DIM, T, true>(x, xq);
+        gauss_interp<DIM, T, true>(v, vq);
         expm1_quot<NV, T>(vq, eps, dq);
 #pragma unroll
         for (int a = 0; a < NV; ++a) dq[a] *= exp(xq[a]);
@@ -480,7 +491,7 @@ __device__ __forceinline__ void elem_scalar_vjp(const T *w, const T *kap, const 
         T vol = (DIM == 3) ? h * h * h : h * h;
         T wq = vol / T(NV);
         T uq[NV], lq[NV], src[NV];
-        gauss_interp<DIM, T>(w, uq);
+        gauss_interp<DIM, T, true>(w, uq);
         gauss_interp<DIM, T>(lam, lq);
 #pragma unroll
         for (int q = 0; q < NV; ++q) lq[q] *= exp(uq[q]);
