@@ -361,7 +361,7 @@ __device__ __forceinline__ void elem_eval(const T (*xe)[NV], const T (*ve)[NV], 
 // Scalar kinds: the 3^DIM neighbourhood of x, v (and e^m) is loaded into
 // registers first (clamped indices, all loads in flight together), then the
 // 2^DIM elements around the node are evaluated from registers.
-template <int DIM, int KIND, int MODE, typename T, typename TV>
+template <int DIM, int KIND, int MODE, int PF, typename T, typename TV>
 __device__ __forceinline__ void node_value_scalar(const Grid &g, const Phys &ph, const T *kap, const T *x,
                                                   const TV *v, const T *Ax, double eps, int X, int Y, int Z,
                                                   long long i, T *val) {
@@ -415,13 +415,13 @@ __device__ __forceinline__ void node_value_scalar(const Grid &g, const Phys &ph,
             ve[0][a] = nv[k];
             kp[a] = nk[k];
         }
-        elem_eval<DIM, KIND, MODE, T, 1, NV>(xe, ve, kp, e, ph, h, r);
+        elem_eval<DIM, KIND, MODE, T, 1, NV, PF>(xe, ve, kp, e, ph, h, r);
         val[0] += r[0][el];
     }
     if constexpr (MODE == M_FD_PLAIN) val[0] = (val[0] - Ax[i]) * (T)(1.0 / eps);
 }
 
-template <int DIM, int KIND, int MODE, typename T, typename TV, class Epi>
+template <int DIM, int KIND, int MODE, typename T, typename TV, int PF, class Epi>
 __global__ __launch_bounds__(BLOCK) void k_node(Grid g, Phys ph, const T *kap, const T *x, const TV *v, const T *Ax,
                                                 FdStep fd, Epi epi, Red red) {
     constexpr int NC = 1;
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(BLOCK) void k_node(Grid g, Phys ph, const T *kap, c
         T val[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) val[c] = T(0);
-        if (!dir) node_value_scalar<DIM, KIND, MODE, T, TV>(g, ph, kap, x, v, Ax, eps, X, Y, Z, i, val);
+        if (!dir) node_value_scalar<DIM, KIND, MODE, PF, T, TV>(g, ph, kap, x, v, Ax, eps, X, Y, Z, i, val);
         T in[Epi::NIN * NC > 0 ? Epi::NIN * NC : 1];
         const PtrAt at{i};
         epi.load(at, in);

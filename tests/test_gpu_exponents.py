@@ -16,7 +16,9 @@ import pytest
 torch = pytest.importorskip('torch')
 pytestmark = pytest.mark.gpu
 
-from _common import make_ctx, to_dev
+from _common import make_ctx, oracle_grid, oracle_problem, rel, to_dev, to_np
+from oracle import derivatives as OD
+from oracle import problems as OP
 from paper_2103_13890_amd import api
 from paper_2103_13890_amd import workloads as W
 
@@ -66,7 +68,7 @@ def test_wave_kernels(kind, params, n):
     w, u, v = _workload(kind, params, n, [(0, 0), (1, 0), (2, 1)], nlevels)
     U, V = to_dev(u), to_dev(v)
 
-    def rel(call):
+    def diff(call):
         a, b = call(2), call(1)
         return float((a - b).norm() / b.norm())
 
@@ -77,10 +79,27 @@ def test_wave_kernels(kind, params, n):
         c = make_ctx(w, kernel_path=path)
         api.mg_setup(c, U)
         return api.mg_smooth(c, top, V, torch.zeros_like(V), 4, True)
-    assert rel(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U)) < 1e-12
-    assert rel(lambda p: api.jfnk_vjp(make_ctx(w, kernel_path=p), top, 0, U, V)) < 1e-12
-    assert rel(lambda p: jv(p, 2, U, V)) < 1e-12
-    assert rel(lambda p: jv(p, 1, U, V)) < 1e-8
-    assert rel(smooth) < 1e-10
-    assert rel(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U.float())) < 1e-4
-    assert rel(lambda p: jv(p, 2, U.float(), V.float())) < 1e-4
+    assert diff(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U)) < 1e-12
+    assert diff(lambda p: api.jfnk_vjp(make_ctx(w, kernel_path=p), top, 0, U, V)) < 1e-12
+    assert diff(lambda p: jv(p, 2, U, V)) < 1e-12
+    assert diff(lambda p: jv(p, 1, U, V)) < 1e-8
+    assert diff(smooth) < 1e-10
+    assert diff(lambda p: api.jfnk_residual(make_ctx(w, kernel_path=p), top, U.float())) < 1e-4
+    assert diff(lambda p: jv(p, 2, U.float(), V.float())) < 1e-4
+
+
+@pytest.mark.parametrize('params', EXPONENTS)
+@pytest.mark.parametrize('n', [(140, 131), (700, 41)])
+def test_2d_fp32_gauss(params, n):
+    """The node kernel's instances on 2D FP32 levels of the Gauss-point kind, against
+    the oracle at the same FP32 state and direction.  The fluxes come from
+    differences of neighbours, which FP32 holds to a rounding: about 4 x 6e-8 of a
+    flux, h / h^2 of which stays in F and J v: 1.7e-4 / 10 at h = 1/700 with
+    second derivatives near 10; 1e-4, the bar of the other FP32 parity tests."""
+    w, u, v = _workload('plap_gauss', params, n, [(0, 0), (1, 1)], 1, fd_form=2)
+    g, pb = oracle_grid(w), oracle_problem(w)
+    ctx = make_ctx(w)
+    U, V = to_dev(u, torch.float32), to_dev(v, torch.float32)
+    u, v = to_np(U), to_np(V)
+    assert rel(to_np(api.jfnk_residual(ctx, 0, U)), OP.residual(pb, g, u, None)) < 1e-4
+    assert rel(to_np(api.jfnk_jv(ctx, 0, U, V)), OD.jvp(pb, g, u, v)) < 1e-4
