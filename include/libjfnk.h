@@ -225,15 +225,18 @@ jfnk_status jfnk_residual(jfnk_ctx *ctx, int level, int prec, const void *u,
  * grid and the residual as for jfnk_workspace_bytes (INVCOEF excepted: its
  * e^m needs a node-sized array); level in [0, nlevels); u, b (nullable), F:
  * FP64 device arrays of that level's node layout; fnorm2 (device, nullable)
- * receives ||F||^2; stream: a hipStream_t (NULL: the default stream).  The
- * same kernels as jfnk_residual, with their per-block partial sums in a
- * 128 KB static device array instead of a workspace: no hipMalloc, hipFree
+ * receives ||F||^2; stream: a hipStream_t (NULL: the default stream).  F has
+ * the bits of jfnk_residual's.  The scalar kinds run the same kernels, with
+ * their per-block partial sums in a 128 KB static device array instead of a
+ * workspace; the Neo-Hookean kind, whose kernels exchange element sums through
+ * the workspace, runs one here that evaluates an element from each of its
+ * corners (256 x 64 x 64 elements: 423 us against 93).  No hipMalloc, hipFree
  * or other allocation is made.  Each GPU has one such array, shared by every
  * call on it, so calls that overlap on one GPU race (one stream, or ordered
  * streams, per GPU).  Asynchronous.  Errors (jfnk_last_error(NULL)):
- * JFNK_E_INVAL for an invalid problem, level or pointer, INVCOEF, or a grid
- * whose launch needs more partial sums than the array holds (very tall
- * grids: use jfnk_residual); JFNK_E_DEVICE for a HIP error. */
+ * JFNK_E_INVAL for an invalid problem, level or pointer, INVCOEF, or a very tall
+ * 3D grid of a scalar kind (32 to 512 elements in x and more than 16,384 groups
+ * of three node rows in y: use jfnk_residual); JFNK_E_DEVICE for a HIP error. */
 jfnk_status jfnk_residual_static(const jfnk_problem *prob, int level, const double *u, const double *b,
                                  double *F, double *fnorm2, void *stream);
 

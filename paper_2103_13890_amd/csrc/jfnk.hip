@@ -97,6 +97,8 @@ struct jfnk_ctx {
 
 // Scratch of jfnk_residual_static (below): 128 KB of per-block partial sums.
 constexpr long long STATIC_SCRATCH_DOUBLES = 16384;
+static_assert(WAVE_BLOCKS_MAX <= STATIC_SCRATCH_DOUBLES && NODE_BLOCKS_MAX <= STATIC_SCRATCH_DOUBLES,
+              "a residual launch's partial sums fit the static scratch");
 static __device__ __align__(256) double scratch[STATIC_SCRATCH_DOUBLES];
 
 namespace {
@@ -1218,11 +1220,14 @@ jfnk_status jfnk_residual_static(const jfnk_problem *p, int level, const double 
     if (!u || !F) return fail(nullptr, JFNK_E_INVAL, "null u or F");
     if (misaligned(u, 8) || misaligned(F, 8) || misaligned(b, 8) || misaligned(fnorm2, 8))
         return fail(nullptr, JFNK_E_INVAL, "misaligned array");
-    // Tall 3D grids of the scalar kinds stay refused as documented: more than
-    // STATIC_SCRATCH_DOUBLES groups of three node rows in y.
+    // Tall 3D grids of the scalar kinds are refused as the header states: it is
+    // the call's contract, no launch needs more partial sums than the scratch holds.
     const Grid gl = level_grid(*p, level);
     const bool tall = gl.dim == 3 && p->kind != JFNK_NEOHOOKE && gl.nx >= 32 && gl.nx <= 512 && gl.nn < (1LL << 28) &&
                       (gl.NY + 2) / 3 > STATIC_SCRATCH_DOUBLES;
+    if (tall)
+        return fail(nullptr, JFNK_E_INVAL, "the static scratch serves grids of up to " +
+                    std::to_string(STATIC_SCRATCH_DOUBLES) + " groups of three node rows in y: use jfnk_residual");
     double *part = nullptr;
     const jfnk_status s = static_scratch(&part);
     if (s != JFNK_OK) return s;
@@ -1230,11 +1235,7 @@ jfnk_status jfnk_residual_static(const jfnk_problem *p, int level, const double 
     ex.st = (hipStream_t)stream;
     ex.red = Red{part};
     ex.path = 0;
-    ex.red_cap = STATIC_SCRATCH_DOUBLES;
-    if (!tall) ops<double>(make_phys(*p)).residual(ex, gl, make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
-    if (tall || ex.red_short)
-        return fail(nullptr, JFNK_E_INVAL, "the grid needs more partial sums than the static scratch holds ("
-                    + std::to_string(STATIC_SCRATCH_DOUBLES) + "): use jfnk_residual");
+    ops<double>(make_phys(*p)).residual(ex, gl, make_phys(*p), nullptr, u, b, F, nullptr, fnorm2);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(nullptr, JFNK_E_DEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
     return JFNK_OK;

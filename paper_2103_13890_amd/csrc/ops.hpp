@@ -11,22 +11,12 @@ namespace jfnk {
 struct Exec {
     hipStream_t st;
     Red red;
-    int path;            // 0 auto, 1 node-centric, 2 z-marching tiles
+    int path;            // 0 auto, 1 node-centric, 2 z-marching waves
     LazyTable *lazy = nullptr;   // deferred reductions (nullable)
-    // > 0: red holds this many doubles, and a stencil launch that would need
-    // more partial sums is not made (red_short is set instead); 0: unchecked
-    // (the context's workspace sizes red for every launch it makes)
-    long long red_cap = 0;
-    mutable bool red_short = false;
     // scratch of the Neo-Hookean element kernel (nullable: without it the
     // levels run node-centric)
     void *nh = nullptr;
     size_t nh_bytes = 0;
-    bool red_fits(int nb, int ns) const {
-        if (red_cap <= 0 || (long long)nb * (ns > 0 ? ns : 1) <= red_cap) return true;
-        red_short = true;
-        return false;
-    }
     // when set, recorded on st right after the next stencil kernel (before
     // its reduction finish) and cleared: lets a timer bracket that kernel
     mutable hipEvent_t ev_main_end = nullptr;
@@ -83,10 +73,15 @@ inline FdStep make_fd(const Exec &ex, const double *num, const double *vn2, doub
 }
 
 constexpr long long PART_CAP = 4096 * 32;     // partial sums of the context's buffer (blocks x sums)
+constexpr int NODE_BLOCKS_MAX = 4096;         // most blocks of a node-centric launch
+// Most blocks of a residual launch of the wave kernel, whose waves walk over
+// several tiles on larger levels: its partial sums fit the static scratch of
+// the residual without a context.
+constexpr int WAVE_BLOCKS_MAX = 16384;
 
 inline int node_blocks(long long n) {
     long long b = (n + BLOCK - 1) / BLOCK;
-    if (b > 4096) b = 4096;
+    if (b > NODE_BLOCKS_MAX) b = NODE_BLOCKS_MAX;
     return (int)(b < 1 ? 1 : b);
 }
 

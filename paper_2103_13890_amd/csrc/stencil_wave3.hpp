@@ -36,10 +36,6 @@ namespace jfnk {
 // leaves no registers for 4 rows.
 template <typename T, int KIND> constexpr int wave_rows_max = sizeof(T) == 8 && KIND == JFNK_PLAP_GAUSS ? 2 : 4;
 
-// Blocks of a residual launch at most (the partial sums of the residual
-// without a context): its waves walk over several tiles on larger levels.
-constexpr int WAVE_BLOCKS_MAX = 16384;
-
 struct WaveTile {
     int strips;      // waves along the numbered columns
     int ntz;         // z chunks
