@@ -55,9 +55,7 @@ template <typename T> __device__ __forceinline__ void nh_settle(T (*r)[8]) {
 }
 
 // Elements up to which eight lanes share an element (k_nh_elem8).
-#ifndef NH_SPLIT_MAX
-#define NH_SPLIT_MAX 32768
-#endif
+constexpr long long NH_SPLIT_MAX = 32768;
 inline bool nh_split(const Grid &g) { return (long long)g.nx * g.ny * g.nz <= NH_SPLIT_MAX; }
 // scratch entries of a level
 inline size_t nh_entries(const Grid &g) {

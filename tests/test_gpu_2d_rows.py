@@ -2,8 +2,9 @@
 oracle: one column short of, at and past a 62-column strip, several strips,
 row counts that leave a remainder with 1, 2 and 4 rows per wavefront, and
 Dirichlet and natural faces.  Every kind with its compile-time and generic
-exponents.  F in FP64 to 1e-12 and in FP32 to 1e-4, J v against the exact
-derivative to 1e-5 (the bars of the other parity tests), and a smoother of
+exponents.  F in FP64 to 1e-12 and in FP32 to 1e-4 (FP32 levels take the node
+kernels), J v against the exact derivative to 1e-5 (the bars of the other parity
+tests), and a smoother of
 degree 3 against the node-centric kernel of the same library (kernel_path 1)
 to 1e-10: two roundings apart, amplified by the polynomial.
 """

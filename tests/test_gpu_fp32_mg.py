@@ -7,12 +7,11 @@ coarse CG (Sec. 2 smoothers and coarse solver; Algorithm 1).  Here each of
 them is compared with the oracle's FP64 algorithm on the same inputs.
 
 * Grid: the p-Laplacian (p = 3, delta = 1e-2) on 128 x 64 x 64 elements,
-  4 levels.  The two finest levels take the FP32 row-tiled kernel (128 and
-  64 elements in x, the second with one-plane z chunks), 32 x 16 x 16 the
-  node kernel, and the 16 x 8 x 8 coarse grid (735 DoFs) the coarse kernel.
+  4 levels.  The three finest levels (128, 64 and 32 elements in x) take the
+  FP32 wave kernel, and the 16 x 8 x 8 coarse grid (735 DoFs) the coarse kernel.
 * 256^3 (the benchmark's finest level): the smoother from s = 0 and from
   s != 0 with degree 4, i.e. the fused first step, the interior step and the
-  fused last step in the benchmark's 256-thread row tiles, against the
+  fused last step in the benchmark's launch shape, against the
   oracle's Chebyshev iteration on the whole grid.
 * Step: fd_root = 1e-2 on every level, so that FD truncation is not the
   difference being measured; with the same step the GPU's difference form
@@ -168,7 +167,7 @@ def test_fp32_transfers(setup128):
 
 
 def test_fp32_smoother_256_bench_shape():
-    """The benchmark's finest level (256^3, FP32 row tiles of 256 threads):
+    """The benchmark's finest level (256^3, FP32):
     degree-4 Chebyshev from s = 0 (fused first step, interior step, fused
     last step: the pre-smoother) and from s != 0 (start, two interior steps,
     last step: the post-smoother), on the whole grid."""

@@ -1,5 +1,5 @@
 """Parity at the full 256^3 benchmark size (16,974,593 nodes), in the launch
-configuration the benchmark times (automatic kernel choice: the row-tiled
+configuration the benchmark times (automatic kernel choice: the wave
 kernels), on 4096 seeded sample nodes the oracle evaluates one by one.
 
 Tolerances (max abs difference over the samples, relative to the largest
@@ -60,7 +60,7 @@ def test_fullsize_residual_and_jv(data, form):
 
 
 def test_residual_beyond_tiled_limit():
-    """A grid past the tiled kernel's limit of 2^28 nodes per array
+    """A grid past the wave kernel's limit of 2^28 nodes per array
     (512 x 768 x 704 elements: 278 M nodes, 2.2 GB per FP64 array), where F(u)
     runs on the node kernel with 64-bit node indices; through the entry point
     that needs no context (the workspace of a context this size is tens of

@@ -117,11 +117,9 @@ def test_jv_f64(kind, path, form):
     assert rel(to_np(Jv), OD.jvp(pb, g, u, v, m)) < 1e-5
 
 
-# Row-tiled kernel shapes: x extents that are a multiple of 64 (the last node
-# column has its own loader), two wavefronts with a partial second one,
-# natural faces on the high sides, several y tiles and z chunks (below 128
-# elements in x, chunks go down to one plane: the 64 x 30 x 31 case asks for
-# more tiles than its 32 planes times its y tiles, so each chunk is one plane).
+# 3D shapes of the tiles: x extents that are a multiple of 64, partial wavefronts,
+# natural faces on the high sides, several y tiles and z chunks (a small level's
+# chunks go down to one plane).
 TILE_CASES = [
     ('plap', (64, 17, 9), W.ALL3),
     ('plap', (64, 30, 31), [(0, 0), (1, 0), (2, 1)]),
@@ -130,8 +128,7 @@ TILE_CASES = [
     ('plap_gauss', (128, 9, 5), [(0, 0), (1, 1), (2, 0)]),
     ('invcoef', (100, 19, 7), [(0, 1), (1, 1), (2, 0)]),
     ('bratu', (33, 9, 13), W.ALL3),
-    # the tiled kernel's widest rows: 512 threads (8 wavefronts) per block,
-    # the last node column (x = 512) finished through the extra-column path
+    # rows of more than eight wavefronts' columns
     ('plap', (512, 10, 10), [(0, 0), (1, 1), (2, 0)]),
     ('invcoef', (512, 9, 11), W.ALL3),
 ]

@@ -1,4 +1,4 @@
-"""Exact VJPs on the tiled (3D) and row (2D) kernels at ragged sizes, against
+"""Exact VJPs on the wave (3D) and row (2D) kernels at ragged sizes, against
 the oracle and, for kinds or sizes that the oracle's 3D formulas do not cover,
 against the node-centric kernel of the same library: row lengths at, below
 and past whole wavefronts, natural faces (the coefficient product has values
