@@ -48,7 +48,7 @@ BYTES_PER_NODE = {
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 STENCIL_SOURCES = ['common.hpp', 'access.hpp', 'elem.hpp', 'reduce.hpp', 'stencil.hpp', 'stencil_2d.hpp',
-                   'stencil_wave3.hpp', 'ops_stencil.inc']
+                   'stencil_nh.hpp', 'stencil_wave3.hpp', 'ops_stencil.inc']
 TRAFFIC_FILES = {'cheb_step_f32': 'cheb_step_f32_plap3d-256_hbm_traffic.md',
                  'resid_f64': 'resid_f64_plap3d-256_hbm_traffic.md'}
 
