@@ -273,7 +273,9 @@ __device__ __forceinline__ void elem_plap_gauss_fd(const T *x, const T *v, T eps
     T G[DIM][NH], Gv[DIM][NH];
     gq_grad<DIM, T>(x, G);
     gq_grad<DIM, T>(v, Gv);
-    const T ih2 = T(1) / (h * h), d2 = T(ph.a1) * T(ph.a1), e2 = T(0.5) * eps;
+    const T ih2 = T(1) / (h * h), d2 = T(ph.a1) * T(ph.a1);
+    // p = 2 is linear: no step enters (one that overflowed or is NaN neither)
+    const T e2 = PF == 2 || (PF == 0 && ph.a0 == 2.0) ? T(0) : T(0.5) * eps;
     T k[NV], dk[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) k[q] = d2 + gq_dot<DIM, T>(G, G, q) * ih2;
